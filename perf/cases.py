@@ -86,15 +86,16 @@ def draw(rng):
         return {"kind": "qchain", "g": round(rng.uniform(1.2, 2.0), 3), "temperature": round(rng.uniform(0.4, 1.0), 3),
                 "dmax": _log_int(rng, 4, 40), "steps": rng.randint(6, 10), "stepping": rng.choice(["whole", "async"])}
     if kind == "serve":
-        return {"kind": "serve", "t": round(rng.uniform(2.1, 2.5), 3), "dmax": rng.randint(9, 44),
-                "steps": rng.randint(20, 30), "requests": rng.randint(2, 6), "slots": rng.randint(2, 4),
-                "precision": rng.choice(["fp16x3", "bf16x6", "fp64"])}
+        precision = rng.choice(["fp16x3", "bf16x6", "fp64"])
+        return {"kind": "serve", "t": round(rng.uniform(2.1, 2.5), 3),
+                "dmax": rng.randint(9, 32 if precision == "fp64" else 44), "steps": rng.randint(20, 30),
+                "requests": rng.randint(2, 6), "slots": rng.randint(2, 4), "precision": precision}
     model = rng.choice(["ising", "potts"])
     obs = rng.random() < 0.25
     precision = rng.choice(["fp64", "fp64", "fp32", "bf16x6"] + ([] if obs else ["fp16x3"]))
     t = rng.uniform(1.8, 2.8) if model == "ising" else rng.uniform(0.8, 1.25)
     return {"kind": "solve", "model": model, "q": 2 if model == "ising" else 3, "t": round(t, 3),
-            "field": 0.0 if model == "ising" and not obs else 0.05, "dmax": _log_int(rng, 4, 32 if obs else 56),
+            "field": 0.0 if model == "ising" and not obs else 0.05, "dmax": _log_int(rng, 4, 32 if obs else 56 if precision == "fp16x3" else 44),
             "steps": rng.randint(10, 30), "precision": precision, "observables": obs,
             "stepping": rng.choice(["whole", "async"])}
 

@@ -31,6 +31,7 @@
 // reproducible.
 #include <math.h>
 #include "common.h"
+#include "jacobi.h"
 #include "../../include/hotrg.h"
 
 namespace hotrg {
@@ -356,6 +357,211 @@ __global__ __launch_bounds__(EIG_JT) void eig_jacobi_kernel(const double* __rest
     }
 }
 
+// ---------------------------------------------------------------- small Cholesky
+
+// Blocked Cholesky factorisation A = L L^T of a symmetric P x P matrix in LDS
+// (P = 16 NF, row stride P + 1; the lower triangle is used), by NF waves.
+// A 16-column panel is factored by wave 0 in registers (lane = row, the
+// pivot row through readlane: no barrier and no LDS on the column chain),
+// the trailing blocks are then updated by all waves on the matrix cores.
+// Pivots below `floor` are raised to it.  linv receives 1 / L_jj, *minp the
+// smallest pivot met.  Ends with a barrier.
+template <int NF>
+__device__ __forceinline__ void chol_blocked(double* A, double floor, double* linv, double* minp) {
+    constexpr int P = 16 * NF, LDA = P + 1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int fr = lane & 15, fk = lane >> 4;
+    if (tid == 0) *minp = 1e300;
+    for (int b = 0; b < NF; ++b) {
+        const int j0 = 16 * b;
+        if (wave == 0) {
+            const int row0 = j0 + lane, row1 = row0 + 64;
+            const bool in0 = row0 < P, in1 = row1 < P;
+            double x[16], y[16];
+#pragma unroll
+            for (int c = 0; c < 16; ++c) {
+                x[c] = in0 ? A[row0 * LDA + j0 + c] : 0.0;
+                y[c] = in1 ? A[row1 * LDA + j0 + c] : 0.0;
+            }
+            double mp = 1e300;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                double piv = readlane_d(x[j], j);
+                mp = fmin(mp, piv);
+                piv = fmax(piv, floor);
+                const double rs = rsqrt_nr(piv);
+                const double inv = rs * rs;
+                const double mx = x[j] * inv, my = y[j] * inv;
+#pragma unroll
+                for (int c = j + 1; c < 16; ++c) {
+                    const double v = readlane_d(x[j], c);
+                    x[c] = fma(-mx, v, x[c]);
+                    y[c] = fma(-my, v, y[c]);
+                }
+                x[j] = lane == j ? piv * rs : x[j] * rs;
+                y[j] *= rs;
+                if (lane == 0) linv[j0 + j] = rs;
+            }
+#pragma unroll
+            for (int c = 0; c < 16; ++c) {
+                if (in0 && (lane >= 16 || c <= lane)) A[row0 * LDA + j0 + c] = x[c];
+                if (in1) A[row1 * LDA + j0 + c] = y[c];
+            }
+            if (lane == 0) *minp = fmin(*minp, mp);
+        }
+        __syncthreads();
+        // trailing blocks (i, j), b < j <= i, dealt to the waves in turn
+        int t = 0;
+        for (int i = b + 1; i < NF; ++i)
+            for (int j = b + 1; j <= i; ++j, ++t) {
+                if (t % NF != wave) continue;
+                d4 acc;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[q] = A[(16 * i + fk + 4 * q) * LDA + 16 * j + fr];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-A[(16 * i + fr) * LDA + j0 + fk + 4 * q],
+                                                               A[(16 * j + fr) * LDA + j0 + fk + 4 * q], acc, 0, 0, 0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) A[(16 * i + fk + 4 * q) * LDA + 16 * j + fr] = acc[q];
+            }
+        __syncthreads();
+    }
+}
+
+// Mailboxes and keys of one workgroup's Jacobi rounds over P columns of P
+// rows; the Cholesky matrix and the mailboxes are never live together.
+template <int NF>
+struct SmallEig {
+    static constexpr int P = 16 * NF, G = P / 2, LDA = P + 1;
+    static constexpr int SLOT = P + 8;   // 8 modulo 16 doubles: the groups of a wave spread over the banks
+    static constexpr int DOUBLES = 2 * G * SLOT > P * LDA ? 2 * G * SLOT : P * LDA;
+    double buf[DOUBLES];
+    double nrm[2 * G];
+    double key[P];
+    double linv[P];
+    double minp;
+    int flag[2];
+};
+
+constexpr double EIG_JAC_TOL2 = 1.6e-29;   // rotate while |a_p.a_q| > 4e-15 |a_p| |a_q|
+
+// ---------------------------------------------------------------- dense eigenproblem
+
+// E of an early step (n <= EIG_PMAX) diagonalised completely, one workgroup:
+// the rows and columns sorted by descending diagonal, the Cholesky factor of
+// E + mu I (mu = 1e-15 Tr E; a thousand times larger while a pivot says that
+// E, whose products may be in a split precision, is not definite to that
+// accuracy), and one-sided Jacobi on the factor's columns: their norms are
+// sqrt(lambda + mu), their directions the eigenvectors, orthogonal whatever
+// the rank of E.  theta[j] descending, S column j the matching eigenvector
+// (row-major n x n).
+//
+// Bound by the rounds' dependent chain (jacobi.h).  The factor's columns are
+// graded and nearly orthogonal, so 7-8 sweeps do (the two-sided method took
+// 10 on E itself), on one matrix instead of two, with one barrier a round
+// instead of two: n = 64 took 876 us two-sided, 262 us now.
+template <int NF>
+__global__ __launch_bounds__(64 * NF) void eig_dense_kernel(const double* __restrict__ E, int n,
+                                                            double* __restrict__ theta, double* __restrict__ S,
+                                                            EigCtl* ctl) {
+    using Sh = SmallEig<NF>;
+    constexpr int P = Sh::P, LDA = Sh::LDA, RL = 2 * NF;
+    __shared__ Sh sh;
+    __shared__ int place[P];    // place[i]: row of E at sorted position i
+    const int tid = threadIdx.x, g = tid >> 3, r = tid & 7;
+    // sorted order of the diagonal, descending, ties by index
+    for (int i = tid; i < P; i += 64 * NF) sh.key[i] = i < n ? E[(long)i * n + i] : 0.0;
+    __syncthreads();
+    double trace = 0.0;
+    for (int i = 0; i < n; ++i) trace += sh.key[i];
+    for (int i = tid; i < n; i += 64 * NF) {
+        const double v = sh.key[i];
+        int rk = 0;
+        for (int j = 0; j < n; ++j) rk += (sh.key[j] > v) || (sh.key[j] == v && j < i);
+        if (!(v == v)) rk = i;   // a non-finite E: any order (the solve is reported as failed)
+        place[rk] = i;
+    }
+    __syncthreads();
+    double mu = 1e-15 * fabs(trace);
+    for (int attempt = 0;; ++attempt) {
+        for (int e = tid; e < P * P; e += 64 * NF) {
+            const int i = e / P, j = e - (e / P) * P;
+            double v = i == j ? 1.0 : 0.0;
+            if (i < n && j < n) {
+                const long a = place[i], b = place[j];
+                v = 0.5 * (E[a * n + b] + E[b * n + a]) + (i == j ? mu : 0.0);
+            }
+            sh.buf[i * LDA + j] = v;
+        }
+        __syncthreads();
+        chol_blocked<NF>(sh.buf, fmax(1e-3 * mu, 1e-280), sh.linv, &sh.minp);
+        const bool good = sh.minp >= 0.25 * mu;
+        __syncthreads();
+        if (good || attempt == 5) break;
+        mu *= 1e3;
+    }
+    double x[RL], y[RL];
+#pragma unroll
+    for (int i = 0; i < RL; ++i) {
+        const int row = r + 8 * i, c = 2 * g;
+        y[i] = row < n && c < n && c <= row ? sh.buf[row * LDA + c] : 0.0;
+        x[i] = row < n && c + 1 < n && c + 1 <= row ? sh.buf[row * LDA + c + 1] : 0.0;
+    }
+    if (tid < 2) sh.flag[tid] = -1;
+    __syncthreads();
+    bool capped;
+    const int G = (n + 1) / 2;
+    const JacobiShared js{sh.buf, sh.nrm, sh.flag, Sh::SLOT};
+    const int rounds = jacobi_rounds<RL>(x, y, js, G, g, r, EIG_JAC_TOL2, EIG_MAX_SWEEPS, capped);
+    double lx = 0.0, ly = 0.0;
+#pragma unroll
+    for (int i = 0; i < RL; ++i) {
+        lx = fma(x[i], x[i], lx);
+        ly = fma(y[i], y[i], ly);
+    }
+    lx = sum8(lx);
+    ly = sum8(ly);
+    if (r == 0 && g < G) {
+        sh.key[2 * g] = ly;
+        sh.key[2 * g + 1] = lx;
+    }
+    __syncthreads();
+    if (g < G) {
+        // descending order, ties by position (an odd n's empty column ranks last)
+        double kx = 0.0, ky = 0.0;
+        for (int j = r; j < 2 * G; j += 8) {
+            const double v = sh.key[j];
+            kx += (v > lx) || (v == lx && j < 2 * g + 1) ? 1.0 : 0.0;
+            ky += (v > ly) || (v == ly && j < 2 * g) ? 1.0 : 0.0;
+        }
+        const int rx = (int)sum8(kx), ry = (int)sum8(ky);
+        const double ix = lx > 0.0 ? 1.0 / sqrt(lx) : 0.0, iy = ly > 0.0 ? 1.0 / sqrt(ly) : 0.0;
+        if (r == 0) {
+            if (rx < n) theta[rx] = lx - mu;
+            if (ry < n) theta[ry] = ly - mu;
+        }
+#pragma unroll
+        for (int i = 0; i < RL; ++i) {
+            const int row = r + 8 * i;
+            if (row < n) {
+                const long o = (long)place[row] * n;
+                if (rx < n) S[o + rx] = x[i] * ix;
+                if (ry < n) S[o + ry] = y[i] * iy;
+            }
+        }
+    }
+    if (tid == 0) {
+        ctl->sweeps = (rounds + 2 * G - 1) / (2 * G);
+        ctl->jac_capped = capped ? 1 : 0;
+    }
+}
+
+template <int NF>
+static void launch_dense(const double* E, int n, const EigWork& w, hipStream_t stream) {
+    hipLaunchKernelGGL((eig_dense_kernel<NF>), dim3(1), dim3(64 * NF), 0, stream, E, n, w.theta, w.S, w.ctl);
+}
+
 // ---------------------------------------------------------------- Ritz rotation
 
 // V_b <- V_b S, W_b <- W_b S for the 32-row block b; then the partial Gram
@@ -639,7 +845,7 @@ __global__ __launch_bounds__(64) void eig_stats_kernel(const double* __restrict_
         stop = ctl->converged ? HOTRG_EIG_CONVERGED : (ctl->stall >= 3 ? HOTRG_EIG_STAGNATED : HOTRG_EIG_PASS_CAP);
         failed = !ctl->converged && !(ctl->resid <= fail_tol);
     }
-    if (!isfinite(theta[0])) failed = true;
+    if (!isfinite(theta[0]) || !isfinite(ctl->trace)) failed = true;
     if (failed && st->status == 0) st->status = HOTRG_EEIG;
     double err;
     if (p == n) {   // every eigenvalue known: discarded weight summed directly
@@ -743,7 +949,14 @@ hipError_t launch_eig_topk(const double* E, int n, int k, int dx, const EigWork&
     if (n <= EIG_PMAX) {
         if (!range.start) return hipSuccess;
         hipLaunchKernelGGL(eig_init_kernel, dim3(1), dim3(256), 0, stream, E, n, (double*)nullptr, 0, 1, seed, w.ctl);
-        hipLaunchKernelGGL(eig_jacobi_kernel, dim3(1), dim3(EIG_JT), 0, stream, E, n, n, w.theta, w.S, w.ctl, 0);
+        switch ((n + 15) / 16) {
+            case 1: launch_dense<1>(E, n, w, stream); break;
+            case 2: launch_dense<2>(E, n, w, stream); break;
+            case 3: launch_dense<3>(E, n, w, stream); break;
+            case 4: launch_dense<4>(E, n, w, stream); break;
+            case 5: launch_dense<5>(E, n, w, stream); break;
+            default: launch_dense<6>(E, n, w, stream); break;
+        }
         hipLaunchKernelGGL(eig_select_kernel, dim3(k), dim3(256), 0, stream, w.S, n, n, dx, k, Ut, Ux);
         hipLaunchKernelGGL(eig_stats_kernel, dim3(1), dim3(64), 0, stream, w.theta, n, n, k, w.ctl, st, step, slot,
                            fail_tol);

@@ -1,0 +1,194 @@
+// One-sided Jacobi on the columns of a small matrix, one workgroup: the
+// shared rounds of the eigensolver's and (same lane helpers) the iTEBD
+// update's decompositions.
+//
+// Columns sit on a line of 2 G positions, two of them in the registers of
+// each group of eight lanes (lane r of a group holds rows r, r + 8, ...).
+// Even rounds pair positions (2g, 2g + 1), odd rounds (2g + 1, 2g + 2), and
+// the two columns of a pair change places after their rotation (odd-even
+// ordering): every pair of columns meets exactly once in 2 G consecutive
+// rounds.  With the exchange a column stays in a group for two rounds and
+// then moves to a neighbour, so a round passes one column per group through
+// LDS (a mailbox per group, two buffers in turn) instead of reading and
+// writing both, has one barrier, and needs no index arithmetic.
+//
+// What bounds a round is its dependent chain: mailbox read, the pair's dot
+// product over eight lanes (three DPP stages), the rotation's angle, the
+// rotation, mailbox write, barrier.  The squared norms travel with the
+// columns (updated by the rotation, recomputed once per sweep), so a round
+// forms one dot product instead of three, and the angle comes from two
+// reciprocal square roots refined from the hardware estimate instead of
+// IEEE divisions and square roots.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace hotrg {
+
+// a double from another lane of the same row through a DPP move of each half
+template <int Ctrl>
+__device__ __forceinline__ double dpp_d(double v) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, Ctrl, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), Ctrl, 0xF, 0xF, true);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
+// sum over an aligned group of eight lanes: partner lane ^1 (quad_perm
+// [1,0,3,2]), ^2 (quad_perm [2,3,0,1]), then the mirror lane 7 - l inside
+// the half-row (the other quad); every lane gets the same bits
+__device__ __forceinline__ double sum8(double v) {
+    v += dpp_d<0xB1>(v);
+    v += dpp_d<0x4E>(v);
+    v += dpp_d<0x141>(v);
+    return v;
+}
+
+// a double of lane l (uniform l) in every lane
+__device__ __forceinline__ double readlane_d(double v, int l) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)(unsigned)u, l);
+    const int hi = __builtin_amdgcn_readlane((int)(unsigned)(u >> 32), l);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
+// 1 / sqrt(x), x > 0 finite: the hardware estimate (relative error 2^-24
+// measured on gfx950) and one third-order step, which leaves rounding errors
+// only; a dependent chain of six operations
+__device__ __forceinline__ double rsqrt_nr(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+// The rotation that makes columns p, q orthogonal (al = p.p, be = q.q,
+// ga = p.q): p' = c p - s q, q' = s p + c q, and t = s / c, by which the
+// squared norms change (al - t ga, be + t ga).  With d = be - al and
+// h = d^2 + 4 ga^2: c^2 = (1 + |d| / sqrt h) / 2, s = sign(d) ga / (c sqrt h)
+// (the smaller of the two angles).  h > 0 whenever the pair passes its
+// rotation test.
+__device__ __forceinline__ void jacobi_angle(double al, double be, double ga, double& c, double& s, double& t) {
+    const double d = be - al;
+    const double h = fma(d, d, 4.0 * (ga * ga));
+    const double y = rsqrt_nr(h);
+    const double c2 = fma(0.5 * fabs(d), y, 0.5);
+    const double w = rsqrt_nr(c2);
+    c = c2 * w;
+    s = (d >= 0.0 ? ga : -ga) * y * w;
+    t = s * w;
+}
+
+struct JacobiShared {
+    double* mail;   // [2][G][slot]: the columns in flight
+    double* nrm;    // [2][G]: their squared norms
+    int* flag;      // [2]: last even / odd round in which a pair rotated (set to -1 before the call)
+    int slot;       // doubles per mailbox slot
+};
+
+// Rounds until 2 G consecutive ones rotate nothing, or max_sweeps sweeps of
+// 2 G rounds have run.  On entry x holds the column at position 2g + 1 and y
+// the one at 2g (RL rows per lane); on return the group holds two columns, of
+// some order and sign.  A pair is rotated while ga^2 > tol2 al be.  Every
+// thread of the workgroup calls it (groups g >= G hold nothing and only join
+// the barriers).  Returns the rounds run; capped: rotations were still being
+// made when the sweep limit ended it.
+template <int RL>
+__device__ int jacobi_rounds(double (&x)[RL], double (&y)[RL], const JacobiShared& sh, int G, int g, int r,
+                             double tol2, int max_sweeps, bool& capped) {
+    const bool act = g < G;
+    const bool last = g == G - 1;
+    const int to_prev = g == 0 ? G - 1 : g - 1, to_next = last ? 0 : g + 1;
+    double nx = 0.0, ny = 0.0;
+    int last_rot = -1;
+    const int m = 2 * G;
+    const int cap = max_sweeps * m;
+    int rd = 0;
+    // one rotation of the pair (x, y); true in the lanes of a rotated pair.
+    // No branch: a pair that passes no test gets the identity.  swap: x and
+    // y change places instead (y negated; a column's sign is free)
+    auto rotate = [&](bool on, bool swap) -> bool {
+        double g0 = x[0] * y[0], g1 = x[1] * y[1];
+#pragma unroll
+        for (int i = 2; i + 1 < RL; i += 2) {
+            g0 = fma(x[i], y[i], g0);
+            g1 = fma(x[i + 1], y[i + 1], g1);
+        }
+        const double ga = sum8(g0 + g1);
+        const bool rot = on && ga * ga > tol2 * (nx * ny);
+        double c, s, t;
+        jacobi_angle(nx, ny, ga, c, s, t);
+        c = rot ? c : (swap ? 0.0 : 1.0);
+        s = rot ? s : (swap ? -1.0 : 0.0);
+        t = rot ? t : 0.0;
+#pragma unroll
+        for (int i = 0; i < RL; ++i) {
+            const double p = x[i], q = y[i];
+            x[i] = fma(c, p, -(s * q));
+            y[i] = fma(s, p, c * q);
+        }
+        const double ax = fma(-t, ga, nx), ay = fma(t, ga, ny);
+        nx = swap ? ay : ax;
+        ny = swap ? ax : ay;
+        return rot;
+    };
+    for (;;) {
+        if (rd % m == 0) {   // the norms, afresh once per sweep
+            double a = 0.0, b = 0.0;
+#pragma unroll
+            for (int i = 0; i < RL; ++i) {
+                a = fma(x[i], x[i], a);
+                b = fma(y[i], y[i], b);
+            }
+            nx = sum8(a);
+            ny = sum8(b);
+        }
+        // even round: x (now at position 2g) leaves to the previous group
+        if (rotate(act, false) && r == 0) sh.flag[0] = rd;
+        if (act) {
+            double* o = sh.mail + to_prev * sh.slot + r;
+#pragma unroll
+            for (int i = 0; i < RL; ++i) o[8 * i] = x[i];
+            if (r == 0) sh.nrm[to_prev] = nx;
+        }
+        __syncthreads();
+        if (act) {
+            const double* o = sh.mail + g * sh.slot + r;
+#pragma unroll
+            for (int i = 0; i < RL; ++i) x[i] = o[8 * i];
+            nx = sh.nrm[g];
+        }
+        last_rot = max(last_rot, sh.flag[0]);
+        // odd round: y (now at position 2g + 2) leaves to the next group.
+        // The last group holds positions 2G - 1 and 0, which are no pair: it
+        // swaps its registers instead, keeps the one and sends the other back
+        if (rotate(act && !last, last) && r == 0) sh.flag[1] = rd + 1;
+        if (act) {
+            double* o = sh.mail + (G + to_next) * sh.slot + r;
+#pragma unroll
+            for (int i = 0; i < RL; ++i) o[8 * i] = y[i];
+            if (r == 0) sh.nrm[G + to_next] = ny;
+        }
+        __syncthreads();
+        if (act) {
+            const double* o = sh.mail + (G + g) * sh.slot + r;
+#pragma unroll
+            for (int i = 0; i < RL; ++i) y[i] = o[8 * i];
+            ny = sh.nrm[G + g];
+        }
+        last_rot = max(last_rot, sh.flag[1]);
+        rd += 2;
+        // the flags read above are written again only after the barrier of
+        // the next round of the same parity: every thread has the same last_rot
+        if (rd - 1 - last_rot >= m) {
+            capped = false;
+            break;
+        }
+        if (rd >= cap) {
+            capped = true;
+            break;
+        }
+    }
+    return rd;
+}
+
+}  // namespace hotrg

@@ -1,0 +1,36 @@
+"""GPU eigensolver of the environment, step by step: the isometry a step
+applied against the environment it was computed from (both read back through
+the C ABI), at the sizes where the kernels' tiling has its edges."""
+import numpy as np
+import pytest
+
+from paper_2602_05900_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def check_pairs(E, U, orth, resid):
+    """U's columns orthonormal and eigenvectors of E (Rayleigh quotients), and
+    no eigenvalue left out above the kept ones."""
+    lam0 = np.linalg.eigvalsh(E)[::-1]
+    k = U.shape[1]
+    scale = max(abs(lam0[0]), 1e-300)
+    th = np.einsum("ij,ij->j", U, E @ U)
+    assert np.abs(U.T @ U - np.eye(k)).max() <= orth
+    assert np.abs(E @ U - U * th).max() <= resid * scale
+    assert np.abs(th - lam0[:k]).max() <= resid * scale
+
+
+# n = Dx^2 at every block count of the dense solver, its remainders and its
+# ends; dy = 1 leaves E of low rank, dy = 4 of full rank
+@pytest.mark.parametrize("dx", range(1, 10))
+@pytest.mark.parametrize("dy", [1, 4])
+def test_dense_environment(gpu_lib, dx, dy):
+    from paper_2602_05900_amd import binding
+    s = binding.Solve(model="custom", tensor=workloads.random_tensor(dx, dy, seed=10 * dx + dy), dmax=96, max_steps=1)
+    s.coarse_grain(1)
+    E, U = s.environment(), s.isometry()
+    assert U.shape == (dx * dx, dx * dx)
+    # a pair stops rotating at 4e-15 of its norms; products over n <= 81 terms round below 81 eps
+    check_pairs(E, U, 5e-14, 5e-14)
+    s.close()

@@ -28,10 +28,11 @@
  * and its timing events.
  *
  * The truncation eigensolve (FP64) runs on the device: environments up to
- * 96 x 96 are diagonalised completely by a parallel two-sided Jacobi method
- * (the 2x2-block rotation scheme of Sec. II.B, Eqs. (5)-(6)); larger ones by
- * a block subspace iteration with Rayleigh-Ritz projection (the small
- * projected problem again by that Jacobi method), warm-started from the
+ * 96 x 96 are diagonalised completely by a one-sided Jacobi method on their
+ * Cholesky factor (the plane rotations of Sec. II.B, Eqs. (5)-(6), in a
+ * systolic pair order); larger ones by a block subspace iteration whose Ritz
+ * vectors come from the singular value decomposition of E V (the same Jacobi
+ * method on the triangular factor of E V), warm-started from the
  * isometry of the step two earlier (the previous step's for steps without
  * the axis exchange), until the kept Ritz pairs have relative residual
  * <= 1e-12, at most 30 passes, or until the residual stagnates (three

@@ -151,17 +151,21 @@ struct EigMail {
 hipError_t launch_eig_mail(const EigCtl* ctl, EigMail* mail, int seq, hipStream_t stream);
 
 constexpr int kEigPMax = 96;   // largest Ritz block / largest fully diagonalised E
+constexpr int kEigRows = 16;   // rows of the Ritz block per workgroup of the eigensolver
 
 // Device buffers of the eigensolver (FP64), carved from the workspace.
 struct EigWork {
     double* V[2];    // Ritz blocks, n x p row-major, one per step parity (warm starts)
-    double* W;       // n x p
-    double* part;    // partial Gram blocks, ceil(n/32) x (kEigPMax^2 + kEigPMax)
-    double* G;       // reduced Gram (+ residuals), kEigPMax^2 + kEigPMax
-    double* S;       // Jacobi eigenvectors, kEigPMax^2
-    double* theta;   // Ritz values, kEigPMax
-    double* L;       // Cholesky factor, kEigPMax^2
-    double* dsc;     // column scales, kEigPMax
+    double* W;       // n x p: E V of a Ritz pass, then the next power pass's block
+    double* Z;       // n x p: E X of a power pass
+    double* part;    // partial Gram tiles, ceil(n/16) x (p/16)(p/16 + 1)/2 x 256
+    double* rpart;   // partial squared residuals for either sign, ceil(n/16) x 2 x kEigPMax
+    double* G;       // summed Gram tiles
+    double* S;       // right singular vectors, or CholeskyQR's Q, kEigPMax^2
+    double* theta;   // sizes of the Ritz values (dense: eigenvalues), descending, kEigPMax
+    double* lam;     // Ritz values with their signs, descending, kEigPMax
+    int* ord;        // the columns of V they belong to, kEigPMax
+    double* dsc;     // column norms, kEigPMax
     EigCtl* ctl;
 };
 
@@ -184,6 +188,9 @@ inline int eig_block(int n, int k) {
 // isometry Ut / Ux (see launch_select_isometry) with the sign gauge; step
 // diagnostics into st.  warm: V[parity] already holds the Ritz block of the
 // step two earlier with the same (n, p).
+// renew: a cold (not warm) solve orthonormalises its block twice in each
+// power pass, so that columns the first time leaves short or inclined (nearly
+// dependent ones) are orthonormal all the same.
 // slot 0 records the diagnostics as the step's own (and eps_left), slot 1 as
 // the right environment's (eps_right, r_*).
 // A solve that stops unconverged with a residual above fail_tol (relative to
@@ -203,7 +210,7 @@ struct EigRange {
 };
 hipError_t launch_eig_topk(const double* E, int n, int k, int dx, const EigWork& w, int parity, bool warm,
                            unsigned long long seed, int maxit, double tol, double fail_tol, const Buf& Ut,
-                           const Buf& Ux, DevState* st, int step, hipStream_t stream, int slot = 0,
+                           const Buf& Ux, DevState* st, int step, hipStream_t stream, bool renew, int slot = 0,
                            const EigRange& range = EigRange());
 
 // Two-sided truncation: when eps_right[step] < eps_left[step], copies the

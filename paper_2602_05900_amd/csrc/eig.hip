@@ -3,29 +3,30 @@
 // The truncation of a HOTRG step keeps the leading k eigenvectors of
 // E = M M^T, to which the higher-order SVD of the merged tensor reduces
 // (Sec. II.A).  Only k << n of them are needed, so for n > P_MAX the solver
-// is a block subspace iteration with a Rayleigh-Ritz projection on every
-// second pass:
+// is a block subspace iteration, alternating power and Ritz passes on an
+// n x p block (p > k):
 //
-//   V (n x p, orthonormal)  ->  W = E V           (MFMA FP64, eig_ev_kernel)
-//   H = V^T W (p x p)       ->  H = S diag(theta) S^T   (Jacobi, one workgroup)
-//   V <- V S, W <- W S      (Ritz vectors; residual |W_j - theta_j V_j|)
-//   converged?  else  V <- orth(W diag(1/|W_j|))  (CholeskyQR)
+//   power:  Z = E X;  G = Z^T Z = D^-1 L L^T D^-1 (columns scaled to unit
+//           norm by D);  V <- Z D L^-T  (CholeskyQR)
+//   Ritz:   W = E V;  G = W^T W = D^-1 L L^T D^-1, so W = Q R with
+//           R^T = D^-1 L;  R^T J = S diag(sigma) by one-sided Jacobi:
+//           S holds the right singular vectors of W = E V, and
+//           u = V S are the Ritz vectors, W S = E u, sigma = |E u|;
+//           residual |E u_j - sigma_j u_j|;  V <- u;  converged? else the
+//           next power pass starts from X = E u / sigma
 //
-// and on the passes between only W = E V and V <- orth(W diag(1/|W_j|)).
-//
-// warm-started from the Ritz block of the step two earlier (same fused leg
+// (sigma_j u_j against E u_j: to first order the same residual as with the
+// Rayleigh quotient.)  Both passes need one Gram matrix, which the product
+// kernel leaves in partial sums, and its Cholesky factor; the Ritz pass
+// costs the Jacobi besides.  R^T is graded with nearly orthogonal columns
+// once V is near the eigenvectors, so the Jacobi takes 3-5 sweeps there.
+// Warm-started from the Ritz block of the step two earlier (same fused leg
 // basis once the dims are steady), else from a counter-based random block.
-// For n <= P_MAX the Jacobi kernel diagonalises E itself.
+// For n <= P_MAX the environment is diagonalised completely.
 //
-// The small symmetric eigenproblem is solved with the paper's two-sided
-// Jacobi scheme (Sec. II.B, Eqs. (5)-(6), Fig. 3): the matrix is cut into
-// 2x2 blocks; each diagonal block M_II is diagonalised by a plane rotation
-// J_I (left = right rotation, the matrix being symmetric); every block
-// M_IJ is then updated as J_I^T M_IJ J_J and the rotations are accumulated;
-// the index pairs then move by the round-robin (systolic) exchange, so that
-// after p-1 rounds every pair has met once (one sweep).  Here one workgroup
-// holds the matrix in LDS and a thread updates whole 2x2 blocks; the
-// "exchange" is a relabelling of which indices form each pair.
+// The rotations are the paper's plane rotations of index pairs (Sec. II.B,
+// Eqs. (5)-(6), Fig. 3), each pair meeting once a sweep in a systolic
+// exchange, applied from one side to a factor of the matrix.
 //
 // All reductions are in a fixed order (no atomics), so a solve is bitwise
 // reproducible.
@@ -37,17 +38,24 @@
 namespace hotrg {
 
 constexpr int EIG_PMAX = kEigPMax; // largest Ritz block / fully diagonalised matrix
-constexpr int EIG_LDP = EIG_PMAX + 1;
-constexpr int EIG_GRAM_ROWS = 32;  // rows per partial Gram block
+constexpr int EIG_ROWS = kEigRows; // rows of the block one workgroup handles
 constexpr int EIG_MAX_SWEEPS = 40;
-// Rayleigh-Ritz (and the convergence test) on every second pass; the pass
-// between is a plain power step V <- orth(E V).  The span of the block, on
-// which convergence depends, is the same either way, and the Jacobi of the
-// Rayleigh quotient dominates a pass: measured at D = 48, 0.66-0.76x the
-// eigensolve time at the same residual bound (every third pass misses the
-// bound in 30 passes).
+// A Ritz pass (and the convergence test) every second pass: the span of the
+// block, on which convergence depends, grows the same way in either, and a
+// Ritz pass costs the Jacobi more (every third pass misses the bound in 30
+// passes).
 constexpr int EIG_RR_EVERY = 2;
-constexpr int EIG_JT = 1024;   // threads of the one-workgroup Jacobi kernel
+// Scaled Gram matrices whose Cholesky pivots stay above EIG_PIV_OK are
+// factored as they are; else (nearly dependent columns: the first pass from
+// a random block, or kept pairs in the rounding noise) with EIG_SHIFT on the
+// diagonal, which bounds |L^-1| by 3e6.
+constexpr double EIG_PIV_OK = 1e-11, EIG_SHIFT = 1e-13;
+// Ritz vectors below this fraction of the largest sigma enter the next power
+// pass as u, not as E u / sigma: the product's rounding (1e-16 of the
+// largest) would leave in E u / sigma a part along the leading vectors that
+// the next product raises to the order of the column itself.
+constexpr double EIG_ADVANCE = 1e-10;
+constexpr double EIG_MU = 1e-15;   // shift of a warm-started solve, relative to Tr E
 
 // ---------------------------------------------------------------- helpers
 
@@ -90,270 +98,171 @@ __global__ __launch_bounds__(256) void eig_init_kernel(const double* __restrict_
     }
     if (!warm) {
         const long total = (long)n * p;
+        const double unit = sqrt(3.0 / n);   // columns of norm about 1
         for (long e = blockIdx.x * 256L + threadIdx.x; e < total; e += (long)gridDim.x * 256)
-            V[e] = hash_uniform(seed * 0x100000001B3ull + (unsigned long long)e);
+            V[e] = unit * hash_uniform(seed * 0x100000001B3ull + (unsigned long long)e);
     }
 }
 
-// ---------------------------------------------------------------- W = E V
+// ---------------------------------------------------------------- Y = E X and its Gram matrix
 
-// Workgroup: 16 rows of W, all p columns; the 4 waves split K and reduce in LDS.
-__global__ __launch_bounds__(256) void eig_ev_kernel(const double* __restrict__ E, int n,
-                                                     const double* __restrict__ V, double* __restrict__ W, int p,
-                                                     const EigCtl* ctl) {
-    if (eig_done(ctl)) return;
-    __shared__ double red[3][16][EIG_PMAX + 1];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int r0 = blockIdx.x * 16;
-    const int fr = lane & 15, fk = lane >> 4;
-    const int nf = p / 16;  // p is a multiple of 16, <= 96
-    d4 acc[6];
+// doubles of one workgroup's partial Gram matrix: the 16 x 16 tiles (i, j),
+// i <= j, of the p x p matrix, in that order
+__host__ __device__ constexpr int gram_tiles(int nf) { return nf * (nf + 1) / 2; }
+__device__ __forceinline__ int gram_tile(int nf, int i, int j) { return i * nf - i * (i - 1) / 2 + (j - i); }
+
+// Gram tiles of 16 staged rows by NW waves, into the workgroup's slot of part.
+template <int NF, int NW>
+__device__ __forceinline__ void gram_rows(const double (*xs)[16 * NF + 2], double* __restrict__ part) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, fr = lane & 15, fk = lane >> 4;
+    double* out = part + (long)blockIdx.x * (gram_tiles(NF) * 256);
+    int t = 0;
 #pragma unroll
-    for (int f = 0; f < 6; ++f) acc[f] = d4{0, 0, 0, 0};
-    const int kchunk = ((n + 63) / 64) * 16;  // multiple of 16 per wave
-    const int kb = wave * kchunk, ke = min(n, kb + kchunk);
-    const int row = r0 + fr;
-    const double* erow = E + (long)min(row, n - 1) * n;
-    // four 4-wide k steps per batch: all loads issued before the MFMAs
-    for (int k = kb; k < ke; k += 16) {
-        double a[4], b[4][6];
+    for (int i = 0; i < NF; ++i)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int kk = k + 4 * u + fk;
-            const bool kin = kk < ke;
-            a[u] = (row < n && kin) ? erow[kk] : 0.0;
+        for (int j = i; j < NF; ++j, ++t) {
+            if (t % NW != wave) continue;
+            d4 g = d4{0, 0, 0, 0};
 #pragma unroll
-            for (int f = 0; f < 6; ++f) b[u][f] = (kin && f < nf) ? V[(long)kk * p + f * 16 + fr] : 0.0;
+            for (int q = 0; q < 4; ++q)
+                g = __builtin_amdgcn_mfma_f64_16x16x4f64(xs[fk + 4 * q][16 * i + fr], xs[fk + 4 * q][16 * j + fr], g, 0,
+                                                         0, 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) out[t * 256 + (fk + 4 * q) * 16 + fr] = g[q];
         }
+}
+
+// Workgroup: EIG_ROWS = 16 rows of Y = (E + mu I) X (n x p, p = 16 NF), all columns;
+// the 8 waves split K, reduce through LDS, and the workgroup's part of
+// Y^T Y follows from the rows while they are there (no pass over Y for it).
+// A lane takes 4 consecutive k of its row per 16 (E read as 32 contiguous
+// bytes a lane, whole lines a wave), the next 16 loaded while the current
+// ones are multiplied.  Bound by those loads' latency at small n and by the
+// reads of E and X at large n: 8.2 / 18 / 40 us at n = 576 / 1024 / 2304,
+// p = 48 / 64 / 80, Gram part included (15.6 / 28 / 68 us, and 9 / 13 / 19 us
+// for a pass over Y, with four waves, no loads ahead and separate kernels).
+template <int NF>
+__global__ __launch_bounds__(512) void eig_ev_kernel(const double* __restrict__ E, int n,
+                                                     const double* __restrict__ X, double* __restrict__ Y,
+                                                     double* __restrict__ part, double mu_rel, const EigCtl* ctl) {
+    if (eig_done(ctl)) return;
+    constexpr int P = 16 * NF, LD = P + 2, NW = 8;
+    const double mu = mu_rel * ctl->trace;
+    typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+    __shared__ double red[NW][EIG_ROWS][LD];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int r0 = blockIdx.x * EIG_ROWS;
+    const int fr = lane & 15, fk = lane >> 4;
+    d4 acc[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) acc[f] = d4{0, 0, 0, 0};
+    const int chunk = ((n + 16 * NW - 1) / (16 * NW)) * 16;
+    const int kb = wave * chunk, ke = min(n, kb + chunk);
+    const double* erow = E + (long)min(r0 + fr, n - 1) * n;
+    auto load = [&](int k, double (&a)[4], double (&b)[4][NF]) {
+        const int k0 = k + 4 * fk;
+        const d2u e0 = *reinterpret_cast<const d2u*>(erow + k0), e1 = *reinterpret_cast<const d2u*>(erow + k0 + 2);
+        a[0] = e0.x;
+        a[1] = e0.y;
+        a[2] = e1.x;
+        a[3] = e1.y;
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int f = 0; f < 6; ++f)
-                if (f < nf) acc[f] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u][f], acc[f], 0, 0, 0);
-    }
-    // component r of lane l holds row (l/16) + 4r, column l%16 of each fragment
-    if (wave > 0) {
-#pragma unroll
-        for (int f = 0; f < 6; ++f)
-            if (f < nf)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) red[wave - 1][fk + 4 * r][f * 16 + fr] = acc[f][r];
-    }
-    __syncthreads();
-    if (wave == 0) {
-#pragma unroll
-        for (int f = 0; f < 6; ++f) {
-            if (f < nf) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int rr = fk + 4 * r;
-                    const double v = acc[f][r] + red[0][rr][f * 16 + fr] + red[1][rr][f * 16 + fr] +
-                                     red[2][rr][f * 16 + fr];
-                    if (r0 + rr < n) W[(long)(r0 + rr) * p + f * 16 + fr] = v;
-                }
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------- Gram partials
-
-// part[b] = X_b^T Y_b over rows [32 b, 32 b + 32) (p x p, row-major).
-__global__ __launch_bounds__(256) void eig_gram_kernel(const double* __restrict__ X, const double* __restrict__ Y,
-                                                       int n, int p, double* __restrict__ part, int part_stride,
-                                                       const EigCtl* ctl) {
-    if (eig_done(ctl)) return;
-    __shared__ double xs[EIG_GRAM_ROWS][EIG_PMAX + 1];
-    __shared__ double ys[EIG_GRAM_ROWS][EIG_PMAX + 1];
-    const int r0 = blockIdx.x * EIG_GRAM_ROWS;
-    for (int e = threadIdx.x; e < EIG_GRAM_ROWS * p; e += 256) {
-        const int r = e / p, c = e - (e / p) * p;
-        const bool in = r0 + r < n;
-        xs[r][c] = in ? X[(long)(r0 + r) * p + c] : 0.0;
-        ys[r][c] = in ? Y[(long)(r0 + r) * p + c] : 0.0;
-    }
-    __syncthreads();
-    double* out = part + (long)blockIdx.x * part_stride;
-    for (int e = threadIdx.x; e < p * p; e += 256) {
-        const int i = e / p, j = e - (e / p) * p;
-        double s = 0.0;
-        for (int r = 0; r < EIG_GRAM_ROWS; ++r) s += xs[r][i] * ys[r][j];
-        out[e] = s;
-    }
-}
-
-// out[e] = sum_b part[b][e], fixed order.
-__global__ __launch_bounds__(256) void eig_reduce_kernel(const double* __restrict__ part, int nb, int part_stride,
-                                                         int count, double* __restrict__ out, const EigCtl* ctl) {
-    if (eig_done(ctl)) return;
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e >= count) return;
-    double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += part[(long)b * part_stride + e];
-    out[e] = s;
-}
-
-// ---------------------------------------------------------------- Jacobi
-
-// Diagonalises the symmetric p x p matrix Hin (p <= EIG_PMAX; read with
-// leading dimension ldh): theta[j] descending, S column j the matching
-// eigenvector (S row-major p x p, S[i*p + j]).  sym: use (H + H^T)/2.
-__global__ __launch_bounds__(EIG_JT) void eig_jacobi_kernel(const double* __restrict__ Hin, int ldh, int p,
-                                                          double* __restrict__ theta, double* __restrict__ S,
-                                                          EigCtl* ctl, int check_done) {
-    if (check_done && eig_done(ctl)) return;
-    __shared__ double H[EIG_PMAX * EIG_LDP];
-    __shared__ double V[EIG_PMAX * EIG_LDP];
-    __shared__ double cs[EIG_PMAX / 2], sn[EIG_PMAX / 2], tt[EIG_PMAX / 2];
-    __shared__ int pi[EIG_PMAX / 2], pj[EIG_PMAX / 2];
-    __shared__ int any_rot;
-    __shared__ double sfloor;
-    __shared__ int rank[EIG_PMAX];
-    const int tid = threadIdx.x;
-    const int pp = p + (p & 1);   // even number of players; index p (if any) is a zero dummy
-    const int half = pp / 2;
-    const int bstride = EIG_JT / half;      // threads per block column
-    // threads 0 .. half*bstride-1 own block column bq and rows bp0, bp0+bstride, ...
-    const int bq = tid < half * bstride ? tid % half : half;
-    const int bp0 = tid / half;
-    for (int e = tid; e < pp * pp; e += EIG_JT) {
-        const int i = e / pp, j = e - (e / pp) * pp;
-        double h = 0.0;
-        if (i < p && j < p) h = 0.5 * (Hin[(long)i * ldh + j] + Hin[(long)j * ldh + i]);
-        H[i * EIG_LDP + j] = h;
-        V[i * EIG_LDP + j] = (i == j) ? 1.0 : 0.0;
-    }
-    if (tid == 0) {
-        double m = 0.0;
-        for (int i = 0; i < p; ++i) m = fmax(m, fabs(Hin[(long)i * ldh + i]));
-        sfloor = fmax(1e-300, 1e-18 * m);
-    }
-    __syncthreads();
-    // Rotation test: an off-diagonal element is zeroed while it is large
-    // relative to its own diagonal pair, |hij| > 1e-14 sqrt|hii hjj| (taken
-    // squared: no square root on the round's critical path), and above
-    // 1e-18 of the largest diagonal element: smaller elements lie under the
-    // rounding of the matrix itself (a rank-deficient tail would otherwise be
-    // rotated until its elements are tiny next to its own tiny diagonal).
-    const double floor_abs = sfloor;
-    auto passes = [&](double hij, double hii, double hjj) {
-        return hij * hij > 1e-28 * fabs(hii * hjj) && fabs(hij) > floor_abs;
+            for (int f = 0; f < NF; ++f) b[u][f] = X[(long)(k0 + u) * P + f * 16 + fr];
     };
-    int sweeps = 0, capped = 0;
-    for (int sweep = 0;; ++sweep) {
-        // A sweep in which no off-diagonal element passes the rotation test
-        // below changes nothing; find that out directly (one pass over the
-        // upper triangle) instead of by running the sweep's pp - 1 rounds.
-        if (tid == 0) any_rot = 0;
-        __syncthreads();
-        for (int e = tid; e < p * p; e += EIG_JT) {
-            const int i = e / p, j = e - (e / p) * p;
-            if (j > i) {
-                if (passes(H[i * EIG_LDP + j], H[i * EIG_LDP + i], H[j * EIG_LDP + j])) any_rot = 1;
+    auto multiply = [&](const double (&a)[4], const double (&b)[4][NF]) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int f = 0; f < NF; ++f) acc[f] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u][f], acc[f], 0, 0, 0);
+    };
+    const int full = ke > kb ? (ke - kb) / 16 : 0;   // whole groups of 16
+    if (full > 0) {
+        double a[4], b[4][NF];
+        load(kb, a, b);
+        for (int i = 1; i < full; ++i) {
+            double a2[4], b2[4][NF];
+            load(kb + 16 * i, a2, b2);
+            multiply(a, b);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                a[u] = a2[u];
+#pragma unroll
+                for (int f = 0; f < NF; ++f) b[u][f] = b2[u][f];
             }
         }
-        __syncthreads();
-        if (!any_rot) break;
-        if (sweep == EIG_MAX_SWEEPS) {   // rotations still pending after the cap
-            capped = 1;
-            break;
-        }
-        for (int r = 0; r < pp - 1; ++r) {
-            // round-robin pairing: position 0 fixed, positions 1..pp-1 rotate by r
-            if (tid < half) {
-                const int qa = tid, qb = pp - 1 - tid;
-                // (q - 1 + r) modulo pp - 1 (both terms below pp - 1), plus 1
-                int a = qa - 1 + r, b = qb - 1 + r;
-                a -= a >= pp - 1 ? pp - 1 : 0;
-                b -= b >= pp - 1 ? pp - 1 : 0;
-                a = qa == 0 ? 0 : a + 1;
-                b += 1;
-                const int i = min(a, b), j = max(a, b);
-                pi[tid] = i;
-                pj[tid] = j;
-                const double hii = H[i * EIG_LDP + i], hjj = H[j * EIG_LDP + j], hij = H[i * EIG_LDP + j];
-                double c = 1.0, s = 0.0, t = 0.0;
-                if (passes(hij, hii, hjj)) {
-                    // the smaller root of t^2 + 2 tau t - 1 = 0, tau = (hjj - hii) / (2 hij),
-                    // written without forming tau: t = sign(d) 2hij / (|d| + sqrt(d^2 + 4 hij^2))
-                    const double d = hjj - hii, h2 = 2.0 * hij;
-                    t = (d >= 0.0 ? h2 : -h2) / (fabs(d) + sqrt(fma(d, d, h2 * h2)));
-                    c = rsqrt(fma(t, t, 1.0));
-                    s = t * c;
-                }
-                cs[tid] = c;
-                sn[tid] = s;
-                tt[tid] = t;
-            }
-            __syncthreads();
-            // two-sided update of every 2x2 block: B' = J_P^T B J_Q; thread
-            // (bq, bp0) handles blocks (P, Q = bq) for P = bp0, bp0 + bstride, ...
-            if (bq < half) {
-                const int k = pi[bq], l = pj[bq];
-                const double cq = cs[bq], sq = sn[bq];
-                for (int P = bp0; P < half; P += bstride) {
-                    const int i = pi[P], j = pj[P];
-                    if (P == bq) {
-                        const double t = tt[P];
-                        if (t != 0.0) {
-                            const double hij = H[i * EIG_LDP + j];
-                            H[i * EIG_LDP + i] -= t * hij;
-                            H[j * EIG_LDP + j] += t * hij;
-                            H[i * EIG_LDP + j] = 0.0;
-                            H[j * EIG_LDP + i] = 0.0;
-                        }
-                        continue;
-                    }
-                    const double cp = cs[P], sp = sn[P];
-                    if (sp == 0.0 && sq == 0.0) continue;   // both rotations are the identity
-                    const double bik = H[i * EIG_LDP + k], bil = H[i * EIG_LDP + l];
-                    const double bjk = H[j * EIG_LDP + k], bjl = H[j * EIG_LDP + l];
-                    // rows: J_P^T
-                    const double rik = cp * bik - sp * bjk, ril = cp * bil - sp * bjl;
-                    const double rjk = sp * bik + cp * bjk, rjl = sp * bil + cp * bjl;
-                    // columns: J_Q
-                    H[i * EIG_LDP + k] = cq * rik - sq * ril;
-                    H[i * EIG_LDP + l] = sq * rik + cq * ril;
-                    H[j * EIG_LDP + k] = cq * rjk - sq * rjl;
-                    H[j * EIG_LDP + l] = sq * rjk + cq * rjl;
-                }
-            }
-            // accumulate: V <- V J (columns k, l of rows bp0, bp0 + bstride, ...)
-            if (bq < half) {
-                const double c = cs[bq], sv = sn[bq];
-                if (sv != 0.0) {
-                    const int k = pi[bq], l = pj[bq];
-                    for (int row = bp0; row < pp; row += bstride) {
-                        const double a = V[row * EIG_LDP + k], b = V[row * EIG_LDP + l];
-                        V[row * EIG_LDP + k] = c * a - sv * b;
-                        V[row * EIG_LDP + l] = sv * a + c * b;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-        sweeps = sweep + 1;
-        __syncthreads();
+        multiply(a, b);
     }
-    // descending order, ties by index
-    for (int i = tid; i < p; i += EIG_JT) {
-        const double ti = H[i * EIG_LDP + i];
-        int rk = 0;
-        for (int j = 0; j < p; ++j) {
-            const double tj = H[j * EIG_LDP + j];
-            rk += (tj > ti) || (tj == ti && j < i);
+    const int kt = kb + 16 * full;
+    if (kt < ke) {   // the last, partial group (n not a multiple of 16)
+        double a[4], b[4][NF];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = kt + 4 * fk + u;
+            const bool in = k < ke;
+            a[u] = in ? erow[k] : 0.0;
+#pragma unroll
+            for (int f = 0; f < NF; ++f) b[u][f] = in ? X[(long)k * P + f * 16 + fr] : 0.0;
         }
-        rank[i] = rk;
+        multiply(a, b);
+    }
+    // component q of lane l holds row (l/16) + 4q, column l%16 of each tile
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) red[wave][fk + 4 * q][f * 16 + fr] = acc[f][q];
+    __syncthreads();
+    for (int e = tid; e < EIG_ROWS * P; e += 512) {
+        const int r = e / P, c = e - (e / P) * P;
+        double v = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v += red[w][r][c];
+        if (r0 + r < n) {
+            v = fma(mu, X[(long)(r0 + r) * P + c], v);
+            Y[(long)(r0 + r) * P + c] = v;
+        } else {
+            v = 0.0;   // rows past n add nothing to the Gram matrix
+        }
+        red[0][r][c] = v;   // read by this thread only, above
     }
     __syncthreads();
-    for (int i = tid; i < p; i += EIG_JT) theta[rank[i]] = H[i * EIG_LDP + i];
-    for (int e = tid; e < p * p; e += EIG_JT) {
-        const int row = e / p, col = e - (e / p) * p;
-        S[(long)row * p + rank[col]] = V[row * EIG_LDP + col];
+    gram_rows<NF, NW>(red[0], part);
+}
+
+// The workgroup's part of X^T X alone.
+template <int NF>
+__global__ __launch_bounds__(64 * NF) void eig_gram_kernel(const double* __restrict__ X, int n,
+                                                           double* __restrict__ part, const EigCtl* ctl) {
+    if (eig_done(ctl)) return;
+    constexpr int P = 16 * NF;
+    __shared__ double xs[EIG_ROWS][P + 2];
+    const long r0 = (long)blockIdx.x * EIG_ROWS;
+    for (int e = threadIdx.x; e < EIG_ROWS * P; e += 64 * NF) {
+        const int r = e / P, c = e - (e / P) * P;
+        xs[r][c] = r0 + r < n ? X[(r0 + r) * P + c] : 0.0;
     }
-    if (tid == 0) {
-        ctl->sweeps = sweeps;
-        ctl->jac_capped = capped;
+    __syncthreads();
+    gram_rows<NF, NF>(xs, part);
+}
+
+// out[e] = sum_b part[b][e] for e < count (a multiple of 32): 32 elements a
+// workgroup, eight threads each, in a fixed order.
+__global__ __launch_bounds__(256) void eig_sum_kernel(const double* __restrict__ part, int nb, int count,
+                                                      double* __restrict__ out, const EigCtl* ctl) {
+    if (eig_done(ctl)) return;
+    __shared__ double sh[8][32];
+    const int c = threadIdx.x & 31, seg = threadIdx.x >> 5;
+    const int e = blockIdx.x * 32 + c;
+    double s = 0.0;
+#pragma unroll 4
+    for (int b = seg; b < nb; b += 8) s += part[(long)b * count + e];
+    sh[seg][c] = s;
+    __syncthreads();
+    if (seg == 0) {
+#pragma unroll
+        for (int i = 1; i < 8; ++i) s += sh[i][c];
+        out[e] = s;
     }
 }
 
@@ -562,218 +471,360 @@ static void launch_dense(const double* E, int n, const EigWork& w, hipStream_t s
     hipLaunchKernelGGL((eig_dense_kernel<NF>), dim3(1), dim3(64 * NF), 0, stream, E, n, w.theta, w.S, w.ctl);
 }
 
-// ---------------------------------------------------------------- Ritz rotation
+// ---------------------------------------------------------------- factor of the Gram matrix
 
-// V_b <- V_b S, W_b <- W_b S for the 32-row block b; then the partial Gram
-// W_b^T W_b and the partial squared residuals |W_j - theta_j V_j|^2 (j < p)
-// into part[b] = [p*p Gram | p residuals].
-__global__ __launch_bounds__(256) void eig_rotate_kernel(double* __restrict__ V, double* __restrict__ W, int n, int p,
-                                                         const double* __restrict__ S, const double* __restrict__ theta,
-                                                         double* __restrict__ part, int part_stride,
-                                                         const EigCtl* ctl) {
-    if (eig_done(ctl)) return;
-    __shared__ double ss[EIG_PMAX * EIG_LDP];
-    __shared__ double vs[EIG_GRAM_ROWS][EIG_PMAX + 1];
-    __shared__ double ws[EIG_GRAM_ROWS][EIG_PMAX + 1];
-    const int r0 = blockIdx.x * EIG_GRAM_ROWS;
-    for (int e = threadIdx.x; e < p * p; e += 256) {
-        const int i = e / p, j = e - (e / p) * p;
-        ss[i * EIG_LDP + j] = S[e];
-    }
-    for (int e = threadIdx.x; e < EIG_GRAM_ROWS * p; e += 256) {
-        const int r = e / p, c = e - (e / p) * p;
-        const bool in = r0 + r < n;
-        vs[r][c] = in ? V[(long)(r0 + r) * p + c] : 0.0;
-        ws[r][c] = in ? W[(long)(r0 + r) * p + c] : 0.0;
-    }
-    __syncthreads();
-    // each thread: outputs (r, c) of both products
-    double vo[12], wo[12];   // EIG_GRAM_ROWS * EIG_PMAX / 256 = 12
-    int cnt = 0;
-    for (int e = threadIdx.x; e < EIG_GRAM_ROWS * p; e += 256, ++cnt) {
-        const int r = e / p, c = e - (e / p) * p;
-        double a = 0.0, b = 0.0;
-        for (int m = 0; m < p; ++m) {
-            const double sm = ss[m * EIG_LDP + c];
-            a += vs[r][m] * sm;
-            b += ws[r][m] * sm;
-        }
-        vo[cnt] = a;
-        wo[cnt] = b;
-    }
-    __syncthreads();
-    cnt = 0;
-    for (int e = threadIdx.x; e < EIG_GRAM_ROWS * p; e += 256, ++cnt) {
-        const int r = e / p, c = e - (e / p) * p;
-        vs[r][c] = vo[cnt];
-        ws[r][c] = wo[cnt];
-        if (r0 + r < n) {
-            V[(long)(r0 + r) * p + c] = vo[cnt];
-            W[(long)(r0 + r) * p + c] = wo[cnt];
-        }
-    }
-    __syncthreads();
-    double* out = part + (long)blockIdx.x * part_stride;
-    for (int e = threadIdx.x; e < p * p; e += 256) {
-        const int i = e / p, j = e - (e / p) * p;
-        double s = 0.0;
-        for (int r = 0; r < EIG_GRAM_ROWS; ++r) s += ws[r][i] * ws[r][j];
-        out[e] = s;
-    }
-    for (int j = threadIdx.x; j < p; j += 256) {
-        const double th = theta[j];
-        double s = 0.0;
-        for (int r = 0; r < EIG_GRAM_ROWS; ++r) {
-            const double d = ws[r][j] - th * vs[r][j];
-            s += d * d;
-        }
-        out[p * p + j] = s;
-    }
-}
-
-// ---------------------------------------------------------------- Cholesky
-
-
-// One workgroup.  G (p x p) is the Gram matrix of the block X to be
-// orthonormalised.  check >= 0: first decide convergence from the reduced
-// residuals (stored after G) of the leading k Ritz pairs; on convergence, or
-// when check == last iteration, mark the solve done and stop.  Then
-// d_j = 1/sqrt(G_jj) (0 for a vanishing column), Gs = D G D (+ shift*I), and
-// Gs = L L^T; Lout receives Q = D L^{-T} (row-major, upper triangular), so
-// that X Q has orthonormal columns, and dout receives d.
-__global__ __launch_bounds__(1024) void eig_chol_kernel(const double* __restrict__ G, int n, int p, int k,
-                                                        const double* __restrict__ theta, double tol, int check,
-                                                        int last_iter, double shift, double* __restrict__ Lout,
-                                                        double* __restrict__ dout, EigCtl* ctl) {
-    if (eig_done(ctl)) return;
-    __shared__ double A[EIG_PMAX * EIG_LDP];
-    __shared__ double d[EIG_PMAX];
-    __shared__ int stop;
+// norm[i] = |Y_i| (0 for a vanishing column) and the factor L of the scaled
+// Gram matrix (unit diagonal) in sh.buf.
+template <int NF>
+__device__ __forceinline__ void factor_gram(const double* __restrict__ Gt, SmallEig<NF>& sh, double* norm) {
+    using Sh = SmallEig<NF>;
+    constexpr int P = Sh::P, LDA = Sh::LDA;
     const int tid = threadIdx.x;
-    if (check >= 0) {
-        if (tid == 0) {
-            double worst = 0.0;
-            for (int j = 0; j < k; ++j) worst = fmax(worst, sqrt(fmax(G[p * p + j], 0.0)));
-            const double scale = fmax(fabs(theta[0]), 1e-300);
-            const int conv = worst <= tol * scale;
-            const double r = worst / scale;
-            ctl->iters = check + 1;
-            ctl->resid = r;
-            ctl->converged = conv;
-            // stagnation: three checks in a row without getting below 0.9x
-            // the best residual so far mean the block has reached its
-            // rounding floor (kept pairs in the noise of a nearly rank-
-            // deficient E); further passes would end at the same residual at
-            // the pass cap, so stop here (converged stays 0, as at the cap)
-            if (r < 0.9 * ctl->best) {
-                ctl->best = r;
-                ctl->stall = 0;
-            } else {
-                ctl->stall += 1;
-            }
-            stop = conv || check == last_iter || ctl->stall >= 3;
-            if (stop) ctl->done = 1;
+    for (int i = tid; i < P; i += 64 * NF) {
+        const double g = Gt[gram_tile(NF, i >> 4, i >> 4) * 256 + (i & 15) * 17];
+        norm[i] = g > 1e-280 ? sqrt(g) : 0.0;
+    }
+    __syncthreads();
+    for (int attempt = 0;; ++attempt) {
+        for (int e = tid; e < P * P; e += 64 * NF) {
+            const int i = e / P, j = e - (e / P) * P;
+            if (j > i) continue;
+            const double dd = norm[i] * norm[j];
+            double v = i == j ? 1.0 : 0.0;
+            if (dd > 0.0 && i != j) v = Gt[gram_tile(NF, j >> 4, i >> 4) * 256 + (j & 15) * 16 + (i & 15)] / dd;
+            if (i == j && attempt) v += EIG_SHIFT;
+            sh.buf[i * LDA + j] = v;
+            if ((i >> 4) == (j >> 4)) sh.buf[j * LDA + i] = v;   // diagonal blocks whole
         }
         __syncthreads();
-        if (stop) return;
-    }
-    for (int j = tid; j < p; j += 1024) {
-        const double g = G[(long)j * p + j];
-        d[j] = g > 1e-280 ? 1.0 / sqrt(g) : 0.0;
-    }
-    __syncthreads();
-    for (int e = tid; e < p * p; e += 1024) {
-        const int i = e / p, j = e - (e / p) * p;
-        double v = 0.5 * (G[(long)i * p + j] + G[(long)j * p + i]) * d[i] * d[j];
-        if (i == j) v = (d[i] == 0.0 ? 1.0 : v) + shift;
-        if (i != j && (d[i] == 0.0 || d[j] == 0.0)) v = 0.0;
-        A[i * EIG_LDP + j] = v;
-    }
-    __syncthreads();
-    // Right-looking Cholesky of the lower triangle with the elimination
-    // applied to the identity beside it, one barrier per column: every thread
-    // takes the pivot L_jj = sqrt(A_jj) itself (A_jj is final at column j);
-    // the trailing update of A scales the column-j entries it needs on the
-    // fly (column j is only read in this phase), and the same row operations
-    // on R (= I at the start) leave R = L^{-1} (rows unscaled until the end:
-    // row j of R is read only at column j, scaled on the fly as well).
-    __shared__ double R[EIG_PMAX * EIG_LDP];
-    __shared__ double ldiag[EIG_PMAX];
-    for (int e = tid; e < p * p; e += 1024) {
-        const int i = e / p, c = e - (e / p) * p;
-        if (c <= i) R[i * EIG_LDP + c] = i == c ? 1.0 : 0.0;
-    }
-    __syncthreads();
-    const int ty = tid >> 5, tx = tid & 31;
-    for (int j = 0; j < p; ++j) {
-        const double a = A[j * EIG_LDP + j];
-        const double ljj = a > 1e-300 ? sqrt(a) : 1.0;
-        const double inv = 1.0 / ljj;
-        if (tid == 0) ldiag[j] = ljj;
-        // thread (ty, tx) of a 32 x 32 grid: rows i = j + 1 + ty, ...; columns
-        // l = j + 1 + tx, ... <= i of A and c = tx, ... <= j of R
-        for (int i = j + 1 + ty; i < p; i += 32) {
-            const double lij = A[i * EIG_LDP + j] * inv;
-            for (int l = j + 1 + tx; l <= i; l += 32) A[i * EIG_LDP + l] -= lij * (A[l * EIG_LDP + j] * inv);
-            for (int c = tx; c <= j; c += 32) R[i * EIG_LDP + c] -= lij * (R[j * EIG_LDP + c] * inv);
-        }
+        chol_blocked<NF>(sh.buf, 0.1 * EIG_SHIFT, sh.linv, &sh.minp);
+        const bool good = attempt || sh.minp >= EIG_PIV_OK;
         __syncthreads();
+        if (good) break;
     }
-    // Q[r][c] = d_r * M[c][r] (X_new = X D L^{-T}), M = L^{-1} = R with row c
-    // scaled by 1 / L_cc; M[c][r] = 0 for r > c
-    for (int e = tid; e < p * p; e += 1024) {
-        const int r = e / p, c = e - (e / p) * p;
-        const double m = r <= c ? R[c * EIG_LDP + r] * (1.0 / ldiag[c]) : 0.0;
-        // a vanishing column is replaced by uniform(-1,1) entries of norm ~ sqrt(n/3)
-        const double dr = d[r] != 0.0 ? d[r] : 1.0 / sqrt(n / 3.0);
-        Lout[e] = dr * m;
-    }
-    for (int j = tid; j < p; j += 1024) dout[j] = d[j];
 }
 
-// X_b <- X_b Q for 32-row blocks, Q = D L^{-T} from eig_chol_kernel (a
-// column with d_j = 0 is first replaced by random entries).  in and out may
-// alias (each block is loaded before it is written).
-__global__ __launch_bounds__(256) void eig_orth_apply_kernel(const double* in, double* out, int n, int p,
-                                                             const double* __restrict__ Q,
-                                                             const double* __restrict__ dsc,
-                                                             unsigned long long seed, const EigCtl* ctl) {
+// Power pass: Q = D L^-T (upper triangular, row-major), so that Z Q has
+// orthonormal columns.  The inverse by 16 x 16 blocks: the diagonal ones by
+// substitution, one lane a row, then wave i the block row i on the matrix
+// cores (a product's result registers are the next one's operand).
+// CholeskyQR's one-workgroup part; the unblocked kernel before it (one
+// barrier a column) took 34 / 72 us at p = 48 / 80; this takes 18 / 38 us.
+template <int NF>
+__global__ __launch_bounds__(64 * NF) void eig_power_kernel(const double* __restrict__ Gt, int n,
+                                                            double* __restrict__ Q, double* __restrict__ dout,
+                                                            const EigCtl* ctl) {
     if (eig_done(ctl)) return;
-    __shared__ double qs[EIG_PMAX * EIG_LDP];
-    __shared__ double xs[EIG_GRAM_ROWS][EIG_PMAX + 1];
-    const int r0 = blockIdx.x * EIG_GRAM_ROWS;
-    for (int e = threadIdx.x; e < p * p; e += 256) {
-        const int i = e / p, j = e - (e / p) * p;
-        qs[i * EIG_LDP + j] = Q[e];
-    }
-    for (int e = threadIdx.x; e < EIG_GRAM_ROWS * p; e += 256) {
-        const int r = e / p, c = e - (e / p) * p;
-        const long gr = r0 + r;
-        double v = 0.0;
-        if (gr < n)
-            v = dsc[c] != 0.0 ? in[gr * p + c]
-                              : hash_uniform(seed ^ (0xD1B54A32D192ED03ull * (unsigned long long)(gr * p + c + 1)));
-        xs[r][c] = v;
+    using Sh = SmallEig<NF>;
+    constexpr int P = Sh::P, LDA = Sh::LDA;
+    __shared__ Sh sh;
+    __shared__ double norm[P];
+    __shared__ double xd[NF][16][17];   // inverses of the diagonal blocks
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int fr = lane & 15, fk = lane >> 4;
+    factor_gram<NF>(Gt, sh, norm);
+    {
+        // row fr of the inverse of diagonal block `wave` (all four lane
+        // groups the same, group 0 stores)
+        const double* Lb = sh.buf + 16 * wave * LDA + 16 * wave;
+        double x[16];
+#pragma unroll
+        for (int i = 15; i >= 0; --i) {
+            double v = i == fr ? 1.0 : 0.0;
+#pragma unroll
+            for (int m = 15; m > i; --m) v = fma(-Lb[m * LDA + i], x[m], v);
+            x[i] = v * sh.linv[16 * wave + i];
+            if (fk == 0) xd[wave][fr][i] = x[i];
+        }
     }
     __syncthreads();
-    double o[12];
-    int cnt = 0;
-    for (int e = threadIdx.x; e < EIG_GRAM_ROWS * p; e += 256, ++cnt) {
-        const int r = e / p, c = e - (e / p) * p;
-        double a = 0.0;
-        for (int m = 0; m <= c; ++m) a += xs[r][m] * qs[m * EIG_LDP + c];   // Q is upper triangular
-        o[cnt] = a;
+    // Block row i = wave of X = L^-1, as its transpose Y_j = X_ij^T, j = i .. 0:
+    //   Y_j = -X_jj^T sum_{j < k <= i} L_kj^T Y_k
+    // (row by row: X L = I holds to rounding, which is what Z D L^-T needs to
+    // be orthonormal where L is nearly singular; solved by columns, L X = I
+    // would)
+    const int i = wave;
+    d4 Yb[NF];
+#pragma unroll
+    for (int j = NF - 1; j >= 0; --j) {
+        if (j > i) continue;
+        if (j == i) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) Yb[j][q] = xd[j][fr][fk + 4 * q];
+        } else {
+            d4 t = d4{0, 0, 0, 0};
+#pragma unroll
+            for (int k = NF - 1; k > j; --k) {
+                if (k > i) continue;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    t = __builtin_amdgcn_mfma_f64_16x16x4f64(sh.buf[(16 * k + fk + 4 * q) * LDA + 16 * j + fr],
+                                                             Yb[k][q], t, 0, 0, 0);
+            }
+            d4 o = d4{0, 0, 0, 0};
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                o = __builtin_amdgcn_mfma_f64_16x16x4f64(-xd[j][fk + 4 * q][fr], t[q], o, 0, 0, 0);
+            Yb[j] = o;
+        }
+        // Q[r][c] = d_r (L^-1)[c][r]; a vanishing column is replaced by
+        // uniform(-1, 1) entries, of norm about sqrt(n / 3)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const double nr = norm[16 * j + fk + 4 * q];
+            const double dr = nr > 0.0 ? 1.0 / nr : 1.0 / sqrt(n / 3.0);
+            Q[(long)(16 * j + fk + 4 * q) * P + 16 * i + fr] = dr * Yb[j][q];
+        }
     }
-    cnt = 0;
-    for (int e = threadIdx.x; e < EIG_GRAM_ROWS * p; e += 256, ++cnt) {
-        const int r = e / p, c = e - (e / p) * p;
-        if (r0 + r < n) out[(long)(r0 + r) * p + c] = o[cnt];
+    for (int i = tid; i < P; i += 64 * NF) dout[i] = norm[i];
+}
+
+// Ritz pass: S (row-major p x p, orthonormal columns) and theta = sigma,
+// descending, of W = E V from the factor of its Gram matrix (see the top).
+// One workgroup, bound by the Jacobi rounds' dependent chain (jacobi.h); the
+// two-sided Jacobi of V^T W it replaces moved two matrices through LDS every
+// round with two barriers, and needed the Cholesky of W^T W besides: 139 + 34
+// us at p = 48, 396 + 72 us at p = 80; this takes 92 / 254 us.
+template <int NF>
+__global__ __launch_bounds__(64 * NF) void eig_ritz_kernel(const double* __restrict__ Gt, double* __restrict__ theta,
+                                                           double* __restrict__ S, EigCtl* ctl) {
+    if (eig_done(ctl)) return;
+    using Sh = SmallEig<NF>;
+    constexpr int P = Sh::P, LDA = Sh::LDA, RL = 2 * NF;
+    __shared__ Sh sh;
+    __shared__ double norm[P];
+    const int tid = threadIdx.x, g = tid >> 3, r = tid & 7;
+    factor_gram<NF>(Gt, sh, norm);
+    double x[RL], y[RL];
+#pragma unroll
+    for (int i = 0; i < RL; ++i) {
+        const int row = r + 8 * i, c = 2 * g;
+        const double w = norm[row] > 0.0 ? norm[row] : 1e-150;
+        y[i] = c <= row ? sh.buf[row * LDA + c] * w : 0.0;
+        x[i] = c + 1 <= row ? sh.buf[row * LDA + c + 1] * w : 0.0;
+    }
+    if (tid < 2) sh.flag[tid] = -1;
+    __syncthreads();
+    bool capped;
+    const JacobiShared js{sh.buf, sh.nrm, sh.flag, Sh::SLOT};
+    const int rounds = jacobi_rounds<RL>(x, y, js, Sh::G, g, r, EIG_JAC_TOL2, EIG_MAX_SWEEPS, capped);
+    double lx = 0.0, ly = 0.0;
+#pragma unroll
+    for (int i = 0; i < RL; ++i) {
+        lx = fma(x[i], x[i], lx);
+        ly = fma(y[i], y[i], ly);
+    }
+    lx = sum8(lx);
+    ly = sum8(ly);
+    if (r == 0) {
+        sh.key[2 * g] = ly;
+        sh.key[2 * g + 1] = lx;
+    }
+    __syncthreads();
+    // descending order, ties by position
+    double kx = 0.0, ky = 0.0;
+    for (int j = r; j < P; j += 8) {
+        const double v = sh.key[j];
+        kx += (v > lx) || (v == lx && j < 2 * g + 1) ? 1.0 : 0.0;
+        ky += (v > ly) || (v == ly && j < 2 * g) ? 1.0 : 0.0;
+    }
+    const int rx = (int)sum8(kx), ry = (int)sum8(ky);
+    const double sx = sqrt(lx), sy = sqrt(ly);
+    if (r == 0) {   // a vanishing column of W: sigma 0, S its unit vector
+        theta[rx] = sx > 1e-140 ? sx : 0.0;
+        theta[ry] = sy > 1e-140 ? sy : 0.0;
+    }
+    const double ix = 1.0 / sx, iy = 1.0 / sy;
+#pragma unroll
+    for (int i = 0; i < RL; ++i) {
+        S[(long)(r + 8 * i) * P + rx] = x[i] * ix;
+        S[(long)(r + 8 * i) * P + ry] = y[i] * iy;
+    }
+    if (tid == 0) {
+        ctl->sweeps = (rounds + P - 1) / P;
+        ctl->jac_capped = capped ? 1 : 0;
+    }
+}
+
+// ---------------------------------------------------------------- block products
+
+// 16 rows of an n x p block in LDS, zeros past n
+template <int NF, typename Fill>
+__device__ __forceinline__ void stage_rows(double (*dst)[16 * NF + 2], const double* src, long r0, int n, Fill fill) {
+    constexpr int P = 16 * NF;
+    for (int e = threadIdx.x; e < EIG_ROWS * P; e += 64 * NF) {
+        const int r = e / P, c = e - (e / P) * P;
+        dst[r][c] = r0 + r < n ? fill(src, r0 + r, c) : 0.0;
+    }
+}
+
+// Power pass: V = Z Q (Q upper triangular), 16 rows a workgroup, one 16-wide
+// column tile a wave.  A column of Z with norm 0 is replaced by random
+// entries.  Z may be V (a workgroup stages its rows before it writes them).
+template <int NF>
+__global__ __launch_bounds__(64 * NF) void eig_orth_kernel(const double* Z, double* V, int n,
+                                                           const double* __restrict__ Q,
+                                                           const double* __restrict__ norm, unsigned long long seed,
+                                                           const EigCtl* ctl) {
+    if (eig_done(ctl)) return;
+    constexpr int P = 16 * NF;
+    __shared__ double zs[EIG_ROWS][P + 2];
+    const int lane = threadIdx.x & 63, f = threadIdx.x >> 6, fr = lane & 15, fk = lane >> 4;
+    const long r0 = (long)blockIdx.x * EIG_ROWS;
+    stage_rows<NF>(zs, Z, r0, n, [&](const double* src, long r, int c) {
+        return norm[c] > 0.0 ? src[r * P + c]
+                             : hash_uniform(seed ^ (0xD1B54A32D192ED03ull * (unsigned long long)(r * P + c + 1)));
+    });
+    __syncthreads();
+    d4 acc = d4{0, 0, 0, 0};
+    for (int kt = 0; kt <= f; ++kt) {
+        double b[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) b[q] = Q[(long)(16 * kt + fk + 4 * q) * P + 16 * f + fr];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(zs[fr][16 * kt + fk + 4 * q], b[q], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (r0 + fk + 4 * q < n) V[(r0 + fk + 4 * q) * P + 16 * f + fr] = acc[q];
+}
+
+// Ritz pass: u = Vin S to V, E u = Win S; the next power pass's block to X
+// (E u / sigma, or u where sigma is too small for it), and the workgroup's
+// parts of |E u_j - sigma_j u_j|^2 and |E u_j + sigma_j u_j|^2 to rpart (the
+// eigenvalue's sign is the one with the smaller residual).  Vin and Win may be V and X (a
+// workgroup stages its rows before it writes them).
+template <int NF>
+__global__ __launch_bounds__(64 * NF) void eig_ritz_apply_kernel(const double* Vin, const double* Win, double* V,
+                                                                 double* X, int n, const double* __restrict__ S,
+                                                                 const double* __restrict__ theta,
+                                                                 double* __restrict__ rpart, const EigCtl* ctl) {
+    if (eig_done(ctl)) return;
+    constexpr int P = 16 * NF;
+    __shared__ double vs[EIG_ROWS][P + 2];
+    __shared__ double ws[EIG_ROWS][P + 2];
+    const int lane = threadIdx.x & 63, f = threadIdx.x >> 6, fr = lane & 15, fk = lane >> 4;
+    const long r0 = (long)blockIdx.x * EIG_ROWS;
+    auto plain = [&](const double* src, long r, int c) { return src[r * P + c]; };
+    stage_rows<NF>(vs, Vin, r0, n, plain);
+    stage_rows<NF>(ws, Win, r0, n, plain);
+    const double sig = theta[16 * f + fr], top = theta[0];
+    __syncthreads();
+    d4 au = d4{0, 0, 0, 0}, aw = d4{0, 0, 0, 0};
+#pragma unroll
+    for (int kt = 0; kt < NF; ++kt) {
+        double b[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) b[q] = S[(long)(16 * kt + fk + 4 * q) * P + 16 * f + fr];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            au = __builtin_amdgcn_mfma_f64_16x16x4f64(vs[fr][16 * kt + fk + 4 * q], b[q], au, 0, 0, 0);
+            aw = __builtin_amdgcn_mfma_f64_16x16x4f64(ws[fr][16 * kt + fk + 4 * q], b[q], aw, 0, 0, 0);
+        }
+    }
+    const bool advance = sig > EIG_ADVANCE * top;
+    const double inv = advance ? 1.0 / sig : 0.0;
+    double res = 0.0, neg = 0.0;   // rows past n are zero in both factors
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const double d = fma(-sig, au[q], aw[q]), e = fma(sig, au[q], aw[q]);
+        res = fma(d, d, res);
+        neg = fma(e, e, neg);
+        const long row = r0 + fk + 4 * q;
+        if (row < n) {
+            V[row * P + 16 * f + fr] = au[q];
+            X[row * P + 16 * f + fr] = advance ? aw[q] * inv : au[q];
+        }
+    }
+    res += __shfl_xor(res, 16, 64);
+    res += __shfl_xor(res, 32, 64);
+    neg += __shfl_xor(neg, 16, 64);
+    neg += __shfl_xor(neg, 32, 64);
+    if (fk == 0) {
+        rpart[(long)blockIdx.x * (2 * EIG_PMAX) + 16 * f + fr] = res;
+        rpart[(long)blockIdx.x * (2 * EIG_PMAX) + EIG_PMAX + 16 * f + fr] = neg;
+    }
+}
+
+// After a Ritz pass: the residuals summed over the workgroups' parts (fixed
+// order), the eigenvalues with their signs in descending order (lam, and ord:
+// the column of V of each; an E computed in a split precision has small
+// negative ones, which rank last although the block finds them by size), and
+// whether the solve stops here.
+__global__ __launch_bounds__(768) void eig_check_kernel(const double* __restrict__ rpart, int nb, int p, int k,
+                                                        const double* __restrict__ theta, double* __restrict__ lam,
+                                                        int* __restrict__ ord, double mu_rel, double tol, int it,
+                                                        int last_iter, EigCtl* ctl) {
+    if (eig_done(ctl)) return;
+    __shared__ double sh[8][EIG_PMAX], sn[8][EIG_PMAX];
+    __shared__ double th[EIG_PMAX];
+    __shared__ double top;
+    const int j = threadIdx.x % EIG_PMAX, seg = threadIdx.x / EIG_PMAX;
+    double s = 0.0, m = 0.0;
+    if (j < p)
+#pragma unroll 4
+        for (int b = seg; b < nb; b += 8) {
+            s += rpart[(long)b * (2 * EIG_PMAX) + j];
+            m += rpart[(long)b * (2 * EIG_PMAX) + EIG_PMAX + j];
+        }
+    sh[seg][j] = s;
+    sn[seg][j] = m;
+    __syncthreads();
+    double mine = 0.0;
+    if (seg == 0) {
+#pragma unroll
+        for (int i = 1; i < 8; ++i) {
+            s += sh[i][j];
+            m += sn[i][j];
+        }
+        mine = j < p ? (m < s ? -theta[j] : theta[j]) : -INFINITY;
+        th[j] = mine;
+    }
+    __syncthreads();
+    if (seg == 0) {
+        int rk = 0;
+        for (int i = 0; i < EIG_PMAX; ++i) rk += (th[i] > mine) || (th[i] == mine && i < j);
+        if (j < p) {
+            lam[rk] = mine - mu_rel * ctl->trace;
+            ord[rk] = j;
+        }
+        if (rk == 0) top = mine;
+        sh[0][j] = j < p && rk < k ? fmin(s, m) : 0.0;
+    }
+    __syncthreads();
+    if (threadIdx.x < 32) sh[0][j] = fmax(sh[0][j], fmax(sh[0][j + 32], sh[0][j + 64]));
+    __syncthreads();
+    for (int h = 16; h > 0; h >>= 1) {
+        if (threadIdx.x < h) sh[0][j] = fmax(sh[0][j], sh[0][j + h]);
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        const double worst = sqrt(fmax(sh[0][0], 0.0));
+        const double scale = fmax(fabs(top), 1e-300);
+        const int conv = worst <= tol * scale;
+        const double res = worst / scale;
+        ctl->iters = it + 1;
+        ctl->resid = res;
+        ctl->converged = conv;
+        // stagnation: three checks in a row without getting below 0.9x
+        // the best residual so far mean the block has reached its
+        // rounding floor (kept pairs in the noise of a nearly rank-
+        // deficient E); further passes would end at the same residual at
+        // the pass cap, so stop here (converged stays 0, as at the cap)
+        if (res < 0.9 * ctl->best) {
+            ctl->best = res;
+            ctl->stall = 0;
+        } else {
+            ctl->stall += 1;
+        }
+        if (conv || it == last_iter || ctl->stall >= 3) ctl->done = 1;
     }
 }
 
 // ---------------------------------------------------------------- output
 
-// Leading k columns of the row-major n x ldv block Vr (descending order):
+// Columns ord[0], ord[1], ... (or 0, 1, ...) of the row-major n x ldv block Vr:
 // largest-magnitude entry made positive (lowest index on ties), written as
 // Ut[l, i] = u_l[i] and Ux[l, a2, a1] = u_l[a1 * dx + a2].
 __device__ __forceinline__ void put_val(const Buf& o, size_t idx, double v) {
@@ -794,15 +845,16 @@ __device__ __forceinline__ void put_val(const Buf& o, size_t idx, double v) {
 }
 
 // One block per kept column l.
-__global__ __launch_bounds__(256) void eig_select_kernel(const double* __restrict__ Vr, int ldv, int n, int dx, int k,
-                                                         Buf Ut, Buf Ux) {
+__global__ __launch_bounds__(256) void eig_select_kernel(const double* __restrict__ Vr, const int* __restrict__ ord,
+                                                         int ldv, int n, int dx, Buf Ut, Buf Ux) {
     __shared__ double sv[256];
     __shared__ int si[256];
     const int l = blockIdx.x;
+    Vr += ord ? ord[l] : l;   // its column
     double best = -1.0;
     int bi = 0x7fffffff;
     for (int i = threadIdx.x; i < n; i += 256) {
-        const double a = fabs(Vr[(long)i * ldv + l]);
+        const double a = fabs(Vr[(long)i * ldv]);
         if (a > best) { best = a; bi = i; }
     }
     sv[threadIdx.x] = best;
@@ -819,9 +871,9 @@ __global__ __launch_bounds__(256) void eig_select_kernel(const double* __restric
         }
         __syncthreads();
     }
-    const double sgn = Vr[(long)si[0] * ldv + l] < 0.0 ? -1.0 : 1.0;
+    const double sgn = Vr[(long)si[0] * ldv] < 0.0 ? -1.0 : 1.0;
     for (int i = threadIdx.x; i < n; i += 256) {
-        const double u = sgn * Vr[(long)i * ldv + l];
+        const double u = sgn * Vr[(long)i * ldv];
         put_val(Ut, (size_t)l * n + i, u);
         const int a1 = i / dx, a2 = i - (i / dx) * dx;
         put_val(Ux, ((size_t)l * dx + a2) * dx + a1, u);
@@ -939,9 +991,43 @@ hipError_t launch_choose_side(DevState* st, int step, void* Ut, void* Ux, const 
     return hipGetLastError();
 }
 
+// One pass of the subspace iteration.  A power pass reads the block the last
+// Ritz pass left in w.W (the first one V itself) and writes V; a Ritz pass
+// reads V (the last pass of an odd limit follows a Ritz pass: it reads w.W).
+template <int NF>
+static void launch_pass(const double* E, int n, int k, const EigWork& w, double* V, int it, int maxit, bool ritz,
+                        double mu, bool twice, double tol, unsigned long long seed, hipStream_t stream) {
+    const int nb = (n + EIG_ROWS - 1) / EIG_ROWS;
+    const int count = gram_tiles(NF) * 256;
+    const bool after_power = it % EIG_RR_EVERY != 0;
+    const double* in = it == 0 || after_power ? V : w.W;
+    double* out = after_power ? w.W : w.Z;
+    hipLaunchKernelGGL((eig_ev_kernel<NF>), dim3(nb), dim3(512), 0, stream, E, n, in, out, w.part,
+                       mu, w.ctl);
+    hipLaunchKernelGGL(eig_sum_kernel, dim3(count / 32), dim3(256), 0, stream, w.part, nb, count, w.G, w.ctl);
+    if (!ritz) {
+        hipLaunchKernelGGL((eig_power_kernel<NF>), dim3(1), dim3(64 * NF), 0, stream, w.G, n, w.S, w.dsc, w.ctl);
+        hipLaunchKernelGGL((eig_orth_kernel<NF>), dim3(nb), dim3(64 * NF), 0, stream, out, V, n, w.S, w.dsc,
+                           seed * 131 + it, w.ctl);
+        if (twice) {
+            hipLaunchKernelGGL((eig_gram_kernel<NF>), dim3(nb), dim3(64 * NF), 0, stream, V, n, w.part, w.ctl);
+            hipLaunchKernelGGL(eig_sum_kernel, dim3(count / 32), dim3(256), 0, stream, w.part, nb, count, w.G, w.ctl);
+            hipLaunchKernelGGL((eig_power_kernel<NF>), dim3(1), dim3(64 * NF), 0, stream, w.G, n, w.S, w.dsc, w.ctl);
+            hipLaunchKernelGGL((eig_orth_kernel<NF>), dim3(nb), dim3(64 * NF), 0, stream, V, V, n, w.S, w.dsc,
+                               seed * 131 + it, w.ctl);
+        }
+        return;
+    }
+    hipLaunchKernelGGL((eig_ritz_kernel<NF>), dim3(1), dim3(64 * NF), 0, stream, w.G, w.theta, w.S, w.ctl);
+    hipLaunchKernelGGL((eig_ritz_apply_kernel<NF>), dim3(nb), dim3(64 * NF), 0, stream, in, out, V, w.W, n, w.S,
+                       w.theta, w.rpart, w.ctl);
+    hipLaunchKernelGGL(eig_check_kernel, dim3(1), dim3(768), 0, stream, w.rpart, nb, 16 * NF, k, w.theta,
+                       w.lam, w.ord, mu, tol, it, maxit - 1, w.ctl);
+}
+
 hipError_t launch_eig_topk(const double* E, int n, int k, int dx, const EigWork& w, int parity, bool warm,
                            unsigned long long seed, int maxit, double tol, double fail_tol, const Buf& Ut,
-                           const Buf& Ux, DevState* st, int step, hipStream_t stream, int slot,
+                           const Buf& Ux, DevState* st, int step, hipStream_t stream, bool renew, int slot,
                            const EigRange& range) {
     if (n < 1 || k < 1 || k > n || maxit < 1) return hipErrorInvalidValue;
     const int it_first = range.first < 0 ? 0 : range.first;
@@ -957,72 +1043,39 @@ hipError_t launch_eig_topk(const double* E, int n, int k, int dx, const EigWork&
             case 5: launch_dense<5>(E, n, w, stream); break;
             default: launch_dense<6>(E, n, w, stream); break;
         }
-        hipLaunchKernelGGL(eig_select_kernel, dim3(k), dim3(256), 0, stream, w.S, n, n, dx, k, Ut, Ux);
+        hipLaunchKernelGGL(eig_select_kernel, dim3(k), dim3(256), 0, stream, w.S,
+                           (const int*)nullptr, n, n, dx, Ut, Ux);
         hipLaunchKernelGGL(eig_stats_kernel, dim3(1), dim3(64), 0, stream, w.theta, n, n, k, w.ctl, st, step, slot,
                            fail_tol);
         return hipGetLastError();
     }
     const int p = eig_block(n, k);
-    if (p <= k || p % 16) return hipErrorInvalidValue;
+    if (p <= k || p % 16 || p < 32 || p > EIG_PMAX) return hipErrorInvalidValue;
     double* V = w.V[parity];
-    const int pstride = EIG_PMAX * EIG_PMAX + EIG_PMAX;
-    const int nb = (n + EIG_GRAM_ROWS - 1) / EIG_GRAM_ROWS;
     const unsigned g_init = grid_for((long)n * p, 256) > 1024 ? 1024 : grid_for((long)n * p, 256);
     if (range.start)
         hipLaunchKernelGGL(eig_init_kernel, dim3(g_init), dim3(256), 0, stream, E, n, V, p, warm ? 1 : 0, seed,
                            w.ctl);
-
-    auto orth = [&](const double* src, double shift1, unsigned long long s2) {
-        // pass 1 (column-scaled, shifted) from src into V, pass 2 in place
-        hipLaunchKernelGGL(eig_gram_kernel, dim3(nb), dim3(256), 0, stream, src, src, n, p, w.part, pstride, w.ctl);
-        hipLaunchKernelGGL(eig_reduce_kernel, dim3(grid_for(p * p, 256)), dim3(256), 0, stream, w.part, nb, pstride,
-                           p * p, w.G, w.ctl);
-        hipLaunchKernelGGL(eig_chol_kernel, dim3(1), dim3(1024), 0, stream, w.G, n, p, k, w.theta, tol, -1, maxit - 1,
-                           shift1, w.L, w.dsc, w.ctl);
-        hipLaunchKernelGGL(eig_orth_apply_kernel, dim3(nb), dim3(256), 0, stream, src, V, n, p, w.L, w.dsc, s2,
-                           w.ctl);
-        hipLaunchKernelGGL(eig_gram_kernel, dim3(nb), dim3(256), 0, stream, V, V, n, p, w.part, pstride, w.ctl);
-        hipLaunchKernelGGL(eig_reduce_kernel, dim3(grid_for(p * p, 256)), dim3(256), 0, stream, w.part, nb, pstride,
-                           p * p, w.G, w.ctl);
-        hipLaunchKernelGGL(eig_chol_kernel, dim3(1), dim3(1024), 0, stream, w.G, n, p, k, w.theta, tol, -1, maxit - 1,
-                           0.0, w.L, w.dsc, w.ctl);
-        hipLaunchKernelGGL(eig_orth_apply_kernel, dim3(nb), dim3(256), 0, stream, V, V, n, p, w.L, w.dsc, s2 + 1,
-                           w.ctl);
-    };
-    const double shift = 1e-13;
-    if (range.start) orth(V, shift, seed * 31 + 7);
+    // warm: E + mu I in place of E (the same eigenvectors), mu far below the
+    // convergence bound: a column of the block in the rounding noise of E
+    // keeps its direction instead of taking that of the noise, which has
+    // fewer dimensions than such columns (it follows the rows of E).  A cold
+    // block has no direction worth keeping; `renew` orthonormalises it twice.
+    const double mu = warm ? EIG_MU : 0.0;
+    const bool twice = renew && !warm;
     for (int it = it_first; it < it_last; ++it) {
-        hipLaunchKernelGGL(eig_ev_kernel, dim3(grid_for(n, 16)), dim3(256), 0, stream, E, n, V, w.W, p, w.ctl);
-        if (it % EIG_RR_EVERY != EIG_RR_EVERY - 1 && it != maxit - 1) {
-            // power step without Rayleigh-Ritz: V <- orth(E V)
-            hipLaunchKernelGGL(eig_gram_kernel, dim3(nb), dim3(256), 0, stream, w.W, w.W, n, p, w.part, pstride,
-                               w.ctl);
-            hipLaunchKernelGGL(eig_reduce_kernel, dim3(grid_for(p * p, 256)), dim3(256), 0, stream, w.part, nb,
-                               pstride, p * p, w.G, w.ctl);
-            hipLaunchKernelGGL(eig_chol_kernel, dim3(1), dim3(1024), 0, stream, w.G, n, p, k, w.theta, tol, -1,
-                               maxit - 1, shift, w.L, w.dsc, w.ctl);
-            hipLaunchKernelGGL(eig_orth_apply_kernel, dim3(nb), dim3(256), 0, stream, w.W, V, n, p, w.L, w.dsc,
-                               seed * 131 + it, w.ctl);
-            continue;
+        const bool ritz = it % EIG_RR_EVERY == EIG_RR_EVERY - 1 || it == maxit - 1;
+        switch (p / 16) {
+            case 2: launch_pass<2>(E, n, k, w, V, it, maxit, ritz, mu, twice, tol, seed, stream); break;
+            case 3: launch_pass<3>(E, n, k, w, V, it, maxit, ritz, mu, twice, tol, seed, stream); break;
+            case 4: launch_pass<4>(E, n, k, w, V, it, maxit, ritz, mu, twice, tol, seed, stream); break;
+            case 5: launch_pass<5>(E, n, k, w, V, it, maxit, ritz, mu, twice, tol, seed, stream); break;
+            default: launch_pass<6>(E, n, k, w, V, it, maxit, ritz, mu, twice, tol, seed, stream); break;
         }
-        hipLaunchKernelGGL(eig_gram_kernel, dim3(nb), dim3(256), 0, stream, V, w.W, n, p, w.part, pstride, w.ctl);
-        hipLaunchKernelGGL(eig_reduce_kernel, dim3(grid_for(p * p, 256)), dim3(256), 0, stream, w.part, nb, pstride,
-                           p * p, w.G, w.ctl);
-        hipLaunchKernelGGL(eig_jacobi_kernel, dim3(1), dim3(EIG_JT), 0, stream, w.G, p, p, w.theta, w.S, w.ctl, 1);
-        hipLaunchKernelGGL(eig_rotate_kernel, dim3(nb), dim3(256), 0, stream, V, w.W, n, p, w.S, w.theta, w.part,
-                           pstride, w.ctl);
-        hipLaunchKernelGGL(eig_reduce_kernel, dim3(grid_for(p * p + p, 256)), dim3(256), 0, stream, w.part, nb,
-                           pstride, p * p + p, w.G, w.ctl);
-        hipLaunchKernelGGL(eig_chol_kernel, dim3(1), dim3(1024), 0, stream, w.G, n, p, k, w.theta, tol, it, maxit - 1,
-                           shift, w.L, w.dsc, w.ctl);
-        // one CholeskyQR pass: the column-scaled Ritz block W is close to
-        // orthonormal, so a second pass is not needed inside the iteration
-        hipLaunchKernelGGL(eig_orth_apply_kernel, dim3(nb), dim3(256), 0, stream, w.W, V, n, p, w.L, w.dsc,
-                           seed * 131 + it, w.ctl);
     }
     if (!range.end) return hipGetLastError();
-    hipLaunchKernelGGL(eig_select_kernel, dim3(k), dim3(256), 0, stream, V, p, n, dx, k, Ut, Ux);
-    hipLaunchKernelGGL(eig_stats_kernel, dim3(1), dim3(64), 0, stream, w.theta, p, n, k, w.ctl, st, step, slot,
+    hipLaunchKernelGGL(eig_select_kernel, dim3(k), dim3(256), 0, stream, V, w.ord, p, n, dx, Ut, Ux);
+    hipLaunchKernelGGL(eig_stats_kernel, dim3(1), dim3(64), 0, stream, w.lam, p, n, k, w.ctl, st, step, slot,
                        fail_tol);
     return hipGetLastError();
 }

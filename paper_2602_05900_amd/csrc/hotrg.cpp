@@ -117,8 +117,8 @@ Fmt y_fmt(Fmt f) { return f == Fmt::BF16x2 || f == Fmt::BF16x3 ? Fmt::F32 : f; }
 struct Layout {
     size_t nT = 0, nP = 0, nAB = 0, nE = 0, nU = 0, nX = 0, nEig = 0;
     int nimp = 0;   // impurity tensors carried (one per observable slot set)
-    size_t oState, oT, oPa, oPb, oAh, oBh, oE, oEigV0, oEigV1, oEigW, oEigPart, oEigG, oEigS, oEigTheta, oEigL,
-        oEigD, oEigCtl, oUt, oUx, oX, oY, total;
+    size_t oState, oT, oPa, oPb, oAh, oBh, oE, oEigV0, oEigV1, oEigW, oEigZ, oEigPart, oEigRes, oEigG, oEigS,
+        oEigTheta, oEigLam, oEigOrd, oEigD, oEigCtl, oUt, oUx, oX, oY, total;
     size_t oI[2] = {0, 0};                                   // impurity tensors (FP64)
     size_t oER = 0, oEigVR0 = 0, oEigVR1 = 0, oUtR = 0, oUxR = 0;  // two-sided
 };
@@ -234,11 +234,16 @@ Layout plan(const hotrg_params* p) {
     L.oEigV0 = take(8 * L.nEig * pb);
     L.oEigV1 = take(8 * L.nEig * pb);
     L.oEigW = take(8 * L.nEig * pb);
-    L.oEigPart = take(8 * ((L.nEig + 31) / 32) * (pb * pb + pb));
-    L.oEigG = take(8 * (pb * pb + pb));
+    const size_t eig_blocks = (L.nEig + kEigRows - 1) / kEigRows;
+    const size_t eig_gram = (pb / 16) * (pb / 16 + 1) / 2 * 256;
+    L.oEigZ = take(8 * L.nEig * pb);
+    L.oEigPart = take(8 * eig_blocks * eig_gram);
+    L.oEigRes = take(8 * eig_blocks * 2 * pb);
+    L.oEigG = take(8 * eig_gram);
     L.oEigS = take(8 * pb * pb);
     L.oEigTheta = take(8 * pb);
-    L.oEigL = take(8 * pb * pb);
+    L.oEigLam = take(8 * pb);
+    L.oEigOrd = take(sizeof(int) * pb);
     L.oEigD = take(8 * pb);
     L.oEigCtl = take(sizeof(EigCtl));
     L.oUt = take(buf_bytes(f, L.nU));
@@ -477,6 +482,7 @@ struct hotrg_solve {
     int pend_next = 0;              // next subspace pass to enqueue
     int pend_par = 0;
     int pend_side = 0;              // two-sided: 0 left eigensolve in flight, 1 right
+    bool pend_warm = false;         // warm start of the left eigensolve, and
     bool pend_warm_r = false;       // warm start of the right eigensolve
     int hist[2] = {0, 0};           // passes the last polled eigensolve of each parity used
     // steps driven by the library's progress thread (hotrg_coarse_grain_async);
@@ -496,11 +502,14 @@ struct hotrg_solve {
         w.V[0] = reinterpret_cast<double*>(ws + L.oEigV0);
         w.V[1] = reinterpret_cast<double*>(ws + L.oEigV1);
         w.W = reinterpret_cast<double*>(ws + L.oEigW);
+        w.Z = reinterpret_cast<double*>(ws + L.oEigZ);
         w.part = reinterpret_cast<double*>(ws + L.oEigPart);
+        w.rpart = reinterpret_cast<double*>(ws + L.oEigRes);
         w.G = reinterpret_cast<double*>(ws + L.oEigG);
         w.S = reinterpret_cast<double*>(ws + L.oEigS);
         w.theta = reinterpret_cast<double*>(ws + L.oEigTheta);
-        w.L = reinterpret_cast<double*>(ws + L.oEigL);
+        w.lam = reinterpret_cast<double*>(ws + L.oEigLam);
+        w.ord = reinterpret_cast<int*>(ws + L.oEigOrd);
         w.dsc = reinterpret_cast<double*>(ws + L.oEigD);
         w.ctl = reinterpret_cast<EigCtl*>(ws + L.oEigCtl);
         return w;
@@ -672,10 +681,17 @@ int enqueue_step(hotrg_solve* s, bool exchange = true, const StepPart& part = St
         const int par = exchange ? (step_index & 1) : 0;
         const int pblk = nE > kEigPMax ? eig_block(nE, Dp) : nE;
         const unsigned long long seed = 0x5EEDull + 7919ull * (unsigned long long)n;
-        const bool warm = nE > kEigPMax && s->warm_n[par] == nE && s->warm_p[par] == pblk;
+        // (a host-polled step keeps the choice taken when its eigensolve began)
+        const bool warm = part.eig.start ? nE > kEigPMax && s->warm_n[par] == nE && s->warm_p[par] == pblk
+                                         : s->pend_warm;
+        // Without the exchange the next step warm-starts from this block and
+        // renews it; its first cold blocks belong to environments of nearly
+        // deficient rank (small Trotter steps), whose surplus columns are
+        // rounding noise either way, and end on stagnation.
+        const bool renew = exchange;
         if (part.left)
             HIP_TRY(s, launch_eig_topk(E, nE, Dp, Dx, s->eig(), par, warm, seed, s->eig_maxit, kEigTol,
-                                       s->eig_fail, Ut, Ux, s->state(), n, s->stream, 0, part.eig));
+                                       s->eig_fail, Ut, Ux, s->state(), n, s->stream, renew, 0, part.eig));
         if (two) {
             // the right eigensolve follows the left one on the same control
             // block; in the host-polled form it starts in a later part, with
@@ -686,13 +702,14 @@ int enqueue_step(hotrg_solve* s, bool exchange = true, const StepPart& part = St
                                     : s->pend_warm_r;
             if (part.right)
                 HIP_TRY(s, launch_eig_topk(ER, nE, Dp, Dx, s->eig_right(), par, warm_r, seed, s->eig_maxit,
-                                           kEigTol, s->eig_fail, UtR, UxR, s->state(), n, s->stream, 1,
+                                           kEigTol, s->eig_fail, UtR, UxR, s->state(), n, s->stream, renew, 1,
                                            part.eigR));
             if (part.rest)
                 HIP_TRY(s, launch_choose_side(s->state(), n, Ut.ptr, Ux.ptr, UtR.ptr, UxR.ptr,
                                               buf_bytes(f, L.nU), s->stream));
             if (part.left && part.eig.start) s->pend_warm_r = warm_r;
         }
+        if (part.left && part.eig.start) s->pend_warm = warm;
         if (nE > kEigPMax && part.left && part.eig.start) {
             s->warm_n[par] = s->warm_nr[par] = nE;
             s->warm_p[par] = s->warm_pr[par] = pblk;

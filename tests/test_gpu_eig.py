@@ -34,3 +34,20 @@ def test_dense_environment(gpu_lib, dx, dy):
     # a pair stops rotating at 4e-15 of its norms; products over n <= 81 terms round below 81 eps
     check_pairs(E, U, 5e-14, 5e-14)
     s.close()
+
+
+# block widths 32, 48, 64, 80, 96; n a multiple of 16, odd, and with a partial
+# last group of rows
+@pytest.mark.parametrize("D", [10, 11, 17, 21, 24, 30, 33, 40, 49])
+def test_subspace_environment(gpu_lib, D):
+    from paper_2602_05900_amd import binding
+    n = 8
+    s = binding.Solve(model="ising", temperature=2.3, dmax=D, max_steps=n)
+    s.coarse_grain(n)
+    assert s.eig_stop(n) == binding.EIG_CONVERGED and s.eig_info(n)[0] > 0
+    E, U = s.environment(), s.isometry()
+    assert U.shape == (D * D, D)
+    # converged pairs: residual at most 1e-12 of the largest eigenvalue; the
+    # vectors are products over p <= 96 of columns orthonormal to 96 x 4e-15
+    check_pairs(E, U, 4e-13, 1.1e-12)
+    s.close()

@@ -305,11 +305,15 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N)
 void gemm_nt_bf16p32_kernel(const __bf16* __restrict__ A, long lda, long a_plane,
                             const __bf16* __restrict__ B, long ldb, long b_plane,
                             int M, int N, int K, Store store, OutMap mp,
-                            int tiles_m, int tiles_n, int per_xcd, int vec)
+                            int tiles_m, int tiles_n, int per_xcd)
 {
     using SP = SplitProducts<NPROD>;
     typedef float f16v __attribute__((ext_vector_type(16)));
     typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+    // the same 16 bytes at the alignment of an element: rows of an odd length
+    // start anywhere, and global loads of 16 bytes take any address
+    typedef unsigned int u4a2 __attribute__((ext_vector_type(4), aligned(2)));
+    typedef unsigned int u4a4 __attribute__((ext_vector_type(4), aligned(4)));
     constexpr int NPL = SP::planes;
     constexpr int BK = 16;
     constexpr int NT = 64 * WAVES_M * WAVES_N;
@@ -350,8 +354,8 @@ void gemm_nt_bf16p32_kernel(const __bf16* __restrict__ A, long lda, long a_plane
     // 8 FP32 values of row `row` from column k (zeros outside), kept raw
     auto fetch_a32 = [&](int nrows, int row, int k, u4 (&dst)[ARP]) {
         const float* base = reinterpret_cast<const float*>(A);
-        if (row < nrows && vec && k + 8 <= K) {
-            const u4* src = reinterpret_cast<const u4*>(base + (long)row * lda + k);
+        if (row < nrows && k + 8 <= K) {
+            const u4a4* src = reinterpret_cast<const u4a4*>(base + (long)row * lda + k);
             dst[0] = src[0];
             dst[1] = src[1];
         } else {
@@ -387,10 +391,10 @@ void gemm_nt_bf16p32_kernel(const __bf16* __restrict__ A, long lda, long a_plane
     };
 
     auto fetch = [&](const __bf16* base, long ld, long pstride, int nrows, int row, int k, u4 (&dst)[NPL]) {
-        if (row < nrows && vec && k + 8 <= K) {
+        if (row < nrows && k + 8 <= K) {
 #pragma unroll
             for (int pl = 0; pl < NPL; ++pl)
-                dst[pl] = *reinterpret_cast<const u4*>(base + pl * pstride + (long)row * ld + k);
+                dst[pl] = *reinterpret_cast<const u4a2*>(base + pl * pstride + (long)row * ld + k);
         } else {
 #pragma unroll
             for (int pl = 0; pl < NPL; ++pl) {
@@ -612,12 +616,10 @@ static hipError_t run_gemm_p32(const Buf& A, long lda, const Buf& B, long ldb, i
     const int per_xcd = (int)((tiles + 7) / 8);
     const long grid = 8L * per_xcd;
     if (grid > 0x7fffffffL) return hipErrorInvalidValue;
-    const bool vec = (AF32 ? lda % 4 == 0 : lda % 8 == 0 && (long)A.plane % 8 == 0) && ldb % 8 == 0 &&
-                     (long)B.plane % 8 == 0 && ((uintptr_t)A.ptr & 15) == 0 && ((uintptr_t)B.ptr & 15) == 0;
     hipLaunchKernelGGL((gemm_nt_bf16p32_kernel<NPROD, BM, BN, WAVES_M, WAVES_N, PF, ROLE, AF32, NBUF>), dim3((unsigned)grid),
                        dim3(64 * WAVES_M * WAVES_N), 0, stream, static_cast<const __bf16*>(A.ptr), lda, (long)A.plane,
                        static_cast<const __bf16*>(B.ptr), ldb, (long)B.plane, M, N, K, st, mp, tiles_m, tiles_n,
-                       per_xcd, vec ? 1 : 0);
+                       per_xcd);
     return hipGetLastError();
 }
 
@@ -1160,6 +1162,31 @@ static hipError_t run_gemm(const T* A, long lda, const T* B, long ldb, int M, in
     return hipGetLastError();
 }
 
+// K not a multiple of 16 (odd bond dimensions, early steps): tiles by the work
+// available, the largest whose grid gives each of the 256 CUs one.  These
+// products are short chains of K steps whose time is the loads' latency, so
+// an emptier chip costs more than the re-reads a smaller tile brings: at
+// D = 21 (BF16x6) env 441^3 272 -> 51 us, Y 9261 x 441 x 441 258 -> 97, X
+// 52 -> 27 against 256 x 256 tiles throughout.  The K order of every
+// element is the same in all of them.
+template <int NPROD, int ROLE>
+static hipError_t dispatch_p32(const Buf& A, long lda, const Buf& B, long ldb, int M, int N, int K, const Store& st,
+                               const OutMap& map, hipStream_t stream)
+{
+    auto grid = [&](long bm, long bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    if (N <= 64) {
+        if (grid(256, 64) >= 256)
+            return run_gemm_p32<NPROD, 256, 64, 4, 1, 1, ROLE>(A, lda, B, ldb, M, N, K, st, map, stream);
+    } else {
+        if (grid(kP32BM, kP32BN) >= 256)
+            return run_gemm_p32<NPROD, kP32BM, kP32BN, kP32WM, kP32WN, kP32PF, ROLE>(A, lda, B, ldb, M, N, K, st, map,
+                                                                                     stream);
+        if (grid(128, 128) >= 256)
+            return run_gemm_p32<NPROD, 128, 128, 2, 2, 1, ROLE>(A, lda, B, ldb, M, N, K, st, map, stream);
+    }
+    return run_gemm_p32<NPROD, 64, 64, 2, 2, 1, ROLE>(A, lda, B, ldb, M, N, K, st, map, stream);
+}
+
 template <int ROLE>
 static hipError_t dispatch(const Buf& A, long lda, const Buf& B, long ldb, int M, int N, int K,
                            const Store& st, const OutMap& map, int products, hipStream_t stream)
@@ -1294,13 +1321,8 @@ static hipError_t dispatch(const Buf& A, long lda, const Buf& B, long ldb, int M
             return run_gemm_dma<6, 256, 256, kDmaWM, kDmaWN, ROLE>(A, lda, B, ldb, M, N, K, st, map,
                                                                               stream, (int)map.ngroup);
         }
-        if (A.fmt == Fmt::BF16x2)
-            return narrow ? run_gemm_p32<3, 256, 64, 4, 1, 1, ROLE>(A, lda, B, ldb, M, N, K, st, map, stream)
-                          : run_gemm_p32<3, kP32BM, kP32BN, kP32WM, kP32WN, kP32PF,
-                                         ROLE>(A, lda, B, ldb, M, N, K, st, map, stream);
-        return narrow ? run_gemm_p32<6, 256, 64, 4, 1, 1, ROLE>(A, lda, B, ldb, M, N, K, st, map, stream)
-                      : run_gemm_p32<6, kP32BM, kP32BN, kP32WM, kP32WN, kP32PF,
-                                     ROLE>(A, lda, B, ldb, M, N, K, st, map, stream);
+        return A.fmt == Fmt::BF16x2 ? dispatch_p32<3, ROLE>(A, lda, B, ldb, M, N, K, st, map, stream)
+                                    : dispatch_p32<6, ROLE>(A, lda, B, ldb, M, N, K, st, map, stream);
     }
     // FP64 / FP32: 64 x 64 tiles for narrow outputs (T', N = D') and where
     // 128 x 128 gives fewer than four tiles per CU (the D = 24 products, the

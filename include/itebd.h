@@ -16,8 +16,8 @@
  *   B2' = rows of Y^T kept, B1' = psi' Y / |S_kept|, lambda_1' = S_kept / |S_kept|
  * after which the two sites exchange roles, so the next update acts on the
  * other bond.  The SVD, in FP64, is a Householder QR with column pivoting,
- * M Pi = Q R, followed by a one-sided (column) Jacobi method with a
- * round-robin pair ordering on R^T: its converged columns, normalised and
+ * M Pi = Q R, followed by a one-sided (column) Jacobi method with an
+ * odd-even pair ordering on R^T: its converged columns, normalised and
  * permuted back by Pi, are the right singular vectors of M and their norms
  * the singular values (Q and the left vectors are never formed).  The kept
  * right vectors have their largest-magnitude entry made positive.
@@ -116,10 +116,11 @@ int itebd_status(itebd_batch* b, int* status);
 int itebd_set_max_sweeps(itebd_batch* b, int max_sweeps);
 
 /* Work done so far, summed over the chains (synchronises): Jacobi sweeps
- * and pair rotations applied.  One sweep over n = 2 chi columns forms the
- * three dot products of every pair (n (n - 1) / 2 pairs, 6 n FLOPs each);
- * a rotation updates two columns of R^T (6 n FLOPs).  Either pointer may
- * be NULL. */
+ * and pair rotations applied.  One sweep over n = 2 chi columns forms every
+ * column's squared norm (2 n FLOPs each) and the dot product of every pair
+ * (n (n - 1) / 2 pairs, 2 n FLOPs each), and a started sweep counts whole; a
+ * rotation updates two columns of R^T (6 n FLOPs).  Either pointer may be
+ * NULL. */
 int itebd_work(itebd_batch* b, double* sweeps, double* rotations);
 
 /* Releases the host handle (waits for the stream first).  NULL is a no-op. */

@@ -37,11 +37,11 @@ def itebd_flops(chi: int, updates: float, sweeps: float, rotations: float) -> fl
     """Algorithmic FLOPs of the device's work (see itebd_work): per update
     the contraction (2 n^2 chi), the gate (32 chi^2), the pivoted QR
     (qr_flops), the singular values (2 n^2) and B1' (4 n chi^2); per sweep
-    the pair dot products (3 n^2 (n - 1)); per rotation 6 n (two columns of
+    the column norms and pair dot products (2 n^2 + n^2 (n - 1)); per rotation 6 n (two columns of
     R^T); n = 2 chi."""
     n = 2 * chi
     per_update = 2 * n * n * chi + 32 * chi * chi + qr_flops(n) + 2 * n * n + 4 * n * chi * chi
-    return updates * per_update + sweeps * 3 * n * n * (n - 1) + rotations * 6 * n
+    return updates * per_update + sweeps * (2 * n * n + n * n * (n - 1)) + rotations * 6 * n
 
 
 def run_itebd(chains: int, chi: int, updates: int, tau: float = 0.01) -> dict:

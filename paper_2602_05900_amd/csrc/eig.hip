@@ -420,9 +420,10 @@ __global__ __launch_bounds__(64 * NF) void eig_dense_kernel(const double* __rest
     if (tid < 2) sh.flag[tid] = -1;
     __syncthreads();
     bool capped;
+    unsigned nrot = 0;
     const int G = (n + 1) / 2;
     const JacobiShared js{sh.buf, sh.nrm, sh.flag, Sh::SLOT};
-    const int rounds = jacobi_rounds<RL>(x, y, js, G, g, r, EIG_JAC_TOL2, EIG_MAX_SWEEPS, capped);
+    const int rounds = jacobi_rounds<RL, false>(x, y, js, G, g, r, EIG_JAC_TOL2, EIG_MAX_SWEEPS, capped, nrot);
     double lx = 0.0, ly = 0.0;
 #pragma unroll
     for (int i = 0; i < RL; ++i) {
@@ -606,8 +607,9 @@ __global__ __launch_bounds__(64 * NF) void eig_ritz_kernel(const double* __restr
     if (tid < 2) sh.flag[tid] = -1;
     __syncthreads();
     bool capped;
+    unsigned nrot = 0;
     const JacobiShared js{sh.buf, sh.nrm, sh.flag, Sh::SLOT};
-    const int rounds = jacobi_rounds<RL>(x, y, js, Sh::G, g, r, EIG_JAC_TOL2, EIG_MAX_SWEEPS, capped);
+    const int rounds = jacobi_rounds<RL, false>(x, y, js, Sh::G, g, r, EIG_JAC_TOL2, EIG_MAX_SWEEPS, capped, nrot);
     double lx = 0.0, ly = 0.0;
 #pragma unroll
     for (int i = 0; i < RL; ++i) {

@@ -26,20 +26,28 @@
 //
 // Lanes: groups of eight lanes, one group per column pair in a Jacobi round
 // and per trailing column (two of them) in a QR step; a lane holds rows
-// l, l + 8, ..., l + 56 of its columns in registers.  A pair's three dot
-// products and a column's reflector product are reduced over the eight lanes
-// with DPP moves (every lane gets the same bits: each stage adds two equal
-// partial sums in either order).  The Jacobi sweep visits all column pairs
-// in n - 1 rounds of n/2 disjoint pairs (round-robin ordering, the systolic
-// schedule of Sec. II.B used for one-sided rotations).  A QR step is one
-// barrier: every wave finds the pivot (the largest remaining column norm,
-// lowest index on ties) and the reflector itself from the norms the previous
-// step left in LDS, keeps the column permutation in registers (lane j holds
-// the storage column of logical column j), and the groups then update the
-// trailing columns and write their new norms for the next step.  The work
-// matrix is column-major with a column stride ld = 8 (mod 32) doubles: the
-// eight groups of a wave read eight consecutive doubles each from columns
-// ld apart, which spreads a wave's read evenly over the banks.
+// l, l + 8, ... of its columns in registers.  A pair's dot product and a
+// column's reflector product are reduced over the eight lanes with DPP moves
+// (every lane gets the same bits).  The Jacobi rounds (jacobi.h) keep the
+// columns in registers and pass one per group through LDS, so the work
+// matrix's LDS is their mailbox while they run.  A QR step is one barrier:
+// every wave finds the pivot (the largest remaining column norm, lowest index
+// on ties) from the squared norms the previous step left in LDS, which is the
+// reflector's squared norm as well, keeps the column permutation in registers
+// (lane j holds the storage column of logical column j), and the groups then
+// update the trailing columns, fetched while the pivot is found, and write
+// their new norms for the next step.  The work matrix is column-major with a
+// column stride ld = 8 (mod 32) doubles: the eight groups of a wave read
+// eight consecutive doubles each from columns ld apart, which spreads a
+// wave's read evenly over the banks.  Rows are held up to the next multiple
+// of eight of n = 2 chi (RL of them a lane), so a small chi does not pay for
+// the largest.
+//
+// What bounds it: the QR steps' and rounds' dependent chains, two chains'
+// waves sharing a SIMD at 512 chains.  512 chains of chi = 30: 520 us an
+// update with two-sided norms, IEEE angles and columns read and written
+// through LDS every round; 360 us now (277 alone on a CU: Jacobi 170, QR 70).
+// 5 chains of chi = 12: 115 us, 74 now.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -47,8 +55,11 @@
 
 #include <algorithm>
 #include <new>
+#include <type_traits>
+#include <utility>
 
 #include "../../include/itebd.h"
+#include "jacobi.h"
 
 namespace {
 
@@ -61,7 +72,6 @@ constexpr int kLd = 72;
 static_assert(kLd >= kMaxN && kLd % 32 == 8, "column stride");
 static_assert(4 * kMaxChi * kMaxChi <= kMaxN * kLd, "B1 and B2 are staged in the work matrix");
 constexpr int kLanes = 8;                       // lanes per Jacobi pair / QR column
-constexpr int kRows = kMaxN / kLanes;           // rows per lane
 constexpr int kGroups = kMaxN / 2;              // lane groups (one per pair of a round)
 constexpr int kUpdThreads = kLanes * kGroups;   // update kernel
 constexpr int kThreads = 256;                   // energy kernel
@@ -69,8 +79,6 @@ static_assert(kMaxN <= 64, "a QR step holds one remaining row or column per lane
 static_assert(2 * kGroups >= kMaxN - 1, "two trailing columns per group cover a QR step");
 // the contraction: one 2 x 2 block of (a, b) per thread
 static_assert(((kMaxChi + 1) / 2) * ((kMaxChi + 1) / 2) <= kUpdThreads, "contraction blocks");
-// the transposition R -> A through registers
-constexpr int kPerThread = (kMaxN * kMaxN + kUpdThreads - 1) / kUpdThreads;
 // the product B1' = P Y_kept: kUpdThreads / n >= 4 groups of n lanes, each
 // lane one row and at most this many kept columns
 constexpr int kMaxColsPerLane = (kMaxChi + 3) / 4;
@@ -83,52 +91,16 @@ struct Gate {
     double g[16];   // exp(-tau h), row-major [(s' t'), (s t)]
 };
 
-// a double from another lane of the same row through a DPP move of each half
-template <int Ctrl>
-__device__ __forceinline__ double dpp_d(double v) {
-    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, Ctrl, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), Ctrl, 0xF, 0xF, false);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
-// sum over an aligned group of eight lanes: partner lane ^1 (quad_perm
-// [1,0,3,2]), ^2 (quad_perm [2,3,0,1]), then the mirror lane 7 - l inside
-// the half-row (the other quad)
-__device__ __forceinline__ double sum8(double v) {
-    v += dpp_d<0xB1>(v);
-    v += dpp_d<0x4E>(v);
-    v += dpp_d<0x141>(v);
-    return v;
-}
-
-// sum over a row of sixteen lanes: sum8, then the mirror lane 15 - l inside
-// the row (the other half-row)
-__device__ __forceinline__ double sum16(double v) {
-    v = sum8(v);
-    v += dpp_d<0x140>(v);
-    return v;
-}
+using hotrg::dpp_d;
+using hotrg::sum8;
+using hotrg::readlane_d;
+using hotrg::wave_max;
+using hotrg::rcp_nr;
+using hotrg::rsqrt_nr;
 
 template <int Ctrl>
 __device__ __forceinline__ int dpp_i(int v) {
     return __builtin_amdgcn_update_dpp(0, v, Ctrl, 0xF, 0xF, false);
-}
-
-// a double of lane l (uniform l) in every lane
-__device__ __forceinline__ double readlane_d(double v, int l) {
-    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)(unsigned)u, l);
-    const int hi = __builtin_amdgcn_readlane((int)(unsigned)(u >> 32), l);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
-// sum over the 64 lanes of a wave: the four row sums (sum16), read from one
-// lane of each row and added in a fixed order, so every lane, and every wave
-// holding the same data, gets the same bits
-__device__ __forceinline__ double wave_sum(double v) {
-    v = sum16(v);
-    return (readlane_d(v, 0) + readlane_d(v, 16)) + (readlane_d(v, 32) + readlane_d(v, 48));
 }
 
 // (v, i) beats (w, j): larger value, lower index on ties
@@ -144,40 +116,28 @@ __device__ __forceinline__ void argmax_step(double& v, int& i) {
     }
 }
 
-// index of the largest value over the wave (lowest index on ties): the same
-// pairings as sum16 inside each row, then the four row winners in order
-__device__ __forceinline__ int wave_argmax(double v, int i) {
-    argmax_step<0xB1>(v, i);
-    argmax_step<0x4E>(v, i);
-    argmax_step<0x141>(v, i);
-    argmax_step<0x140>(v, i);
-    double bv = readlane_d(v, 0);
-    int bi = __builtin_amdgcn_readlane(i, 0);
-#pragma unroll
-    for (int w = 1; w < 4; ++w) {
-        const double ov = readlane_d(v, 16 * w);
-        const int oi = __builtin_amdgcn_readlane(i, 16 * w);
-        if (beats(ov, oi, bv, bi)) {
-            bv = ov;
-            bi = oi;
-        }
-    }
-    return bi;
+template <typename F, int... B>
+__device__ __forceinline__ void qr_blocks(F&& f, std::integer_sequence<int, B...>) {
+    (f(std::integral_constant<int, B>()), ...);
 }
 
+// RL: rows per lane of an eight-lane group, 8 RL >= n = 2 chi
+template <int RL>
 __global__ __launch_bounds__(kUpdThreads) __attribute__((amdgpu_waves_per_eu(2)))
 void itebd_update_kernel(double* __restrict__ states, double* __restrict__ pair, int* __restrict__ status,
                          int* __restrict__ sweeps_out, unsigned long long* __restrict__ work, int chi, Gate G,
                          int nupd, int max_sweeps)
 {
-    __shared__ double sA[kMaxN * kLd];      // work matrix, column-major, stride kLd; stages B1 and B2
+    __shared__ double sA[kMaxN * kLd];      // work matrix, column-major, stride kLd; stages B1 and B2;
+                                             // the Jacobi rounds' mailboxes (2 kGroups slots of kLd)
     __shared__ double sl1[kMaxChi], sl2[kMaxChi];
     __shared__ double sG[16];                // the gate (read from LDS: no long-lived scalar copies)
     __shared__ double scn[2][kMaxN];         // squared norms of the remaining columns, by QR step parity
     __shared__ double sdiag[kMaxN];          // diagonal of R
     __shared__ double ssig[kMaxN], ssgn[kMaxChi], sscale[kMaxChi];
     __shared__ int scol[kMaxN], sinv[kMaxN], sord[kMaxChi];
-    __shared__ int srot;
+    __shared__ double smail_nrm[2 * kGroups];
+    __shared__ int sflag[2];
     __shared__ unsigned long long srotc;
     __shared__ double snrm;
 
@@ -189,10 +149,7 @@ void itebd_update_kernel(double* __restrict__ states, double* __restrict__ pair,
     const long len = 2L * nb + 2 * chi;
     double* st = states + (long)blockIdx.x * len;        // B1 and B2 are rewritten every update
     double* gP = pair + (long)blockIdx.x * n * n;        // P, column-major: P[(a s),(t b)] at (t b) n + (a s)
-    const int lane = tid & 63;
-    const int g = tid / kLanes, r = tid % kLanes;
     const int ng = kUpdThreads / n;                      // lane groups of the row-parallel product (>= 4)
-    const int prow = tid % n, pgrp = tid / n;
 
     for (int i = tid; i < chi; i += kUpdThreads) {
         sl1[i] = st[2 * nb + i];
@@ -206,6 +163,16 @@ void itebd_update_kernel(double* __restrict__ states, double* __restrict__ pair,
     unsigned long long tot_sweeps = 0;
     unsigned nrot = 0;   // rotations of this lane's group (counted by its lane 0)
     for (int u = 0; u < nupd; ++u) {
+        // The thread's coordinates, opaque to the compiler in every update:
+        // it would otherwise keep each phase's addresses and masks, which
+        // depend on nothing else, in registers throughout the loop (the
+        // kernel then spilled 43 of its 256)
+        int tid_u = threadIdx.x;
+        asm volatile("" : "+v"(tid_u));
+        const int tid = tid_u;
+        const int lane = tid & 63;
+        const int g = tid / kLanes, r = tid % kLanes;
+        const int prow = tid % n, pgrp = tid / n;
         // stage B1 and B2 in the work matrix
         double* sB1 = sA;
         double* sB2 = sA + nb;
@@ -225,6 +192,7 @@ void itebd_update_kernel(double* __restrict__ states, double* __restrict__ pair,
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[e] = 0.0;
             const bool a1 = a0 + 1 < chi, b1 = b0 + 1 < chi;
+#pragma unroll 2
             for (int c = 0; c < chi; ++c) {
                 double x[2][2], y[2][2];   // x[a'][s], y[t][b']
 #pragma unroll
@@ -267,8 +235,9 @@ void itebd_update_kernel(double* __restrict__ states, double* __restrict__ pair,
         __syncthreads();   // the staged B1, B2 are no longer needed
         // W = diag(lambda_2 (x) 1) P into the work matrix, rows n.. of its
         // columns zero
-        for (int idx = tid; idx < n * (kMaxN - n); idx += kUpdThreads) {
-            const int j = idx / (kMaxN - n), i = n + idx - j * (kMaxN - n);
+        const int pad = 8 * RL - n;
+        for (int idx = tid; idx < n * pad; idx += kUpdThreads) {
+            const int j = idx / pad, i = n + idx - j * pad;
             sA[j * ld + i] = 0.0;
         }
         if (blk) {
@@ -292,7 +261,7 @@ void itebd_update_kernel(double* __restrict__ states, double* __restrict__ pair,
             if (l < n) {
                 double s2 = 0.0;
 #pragma unroll
-                for (int m = 0; m < kRows; ++m) {
+                for (int m = 0; m < RL; ++m) {
                     const double a = sA[l * ld + r + kLanes * m];
                     s2 = fma(a, a, s2);
                 }
@@ -304,210 +273,185 @@ void itebd_update_kernel(double* __restrict__ states, double* __restrict__ pair,
 
         // Householder QR with column pivoting, one barrier per step
         int col = lane;   // storage column of logical column `lane` (the same in every wave)
-        for (int k = 0; k < n - 1; ++k) {
-            const int cur = k & 1, nxt = cur ^ 1;
-            // storage columns of this group's trailing logical columns k + 1 + g and
-            // k + 1 + g + kGroups before this step's swap (fetched while the pivot is found)
-            const int l0 = k + 1 + g, l1 = l0 + kGroups;
-            const int cb0 = __shfl(col, min(l0, n - 1), 64), cb1 = __shfl(col, min(l1, n - 1), 64);
-            // pivot: the largest remaining norm, lowest logical index on ties
-            int jm = wave_argmax((lane >= k && lane < n) ? scn[cur][lane] : -1.0, lane);
-            if (jm < k || jm >= n) jm = k;   // only with non-finite norms
-            const int colk = __builtin_amdgcn_readlane(col, k), coljm = __builtin_amdgcn_readlane(col, jm);
-            col = lane == k ? coljm : (lane == jm ? colk : col);
-            // the reflector H = I - beta v v^T mapping rows k.. of the pivot column to (alpha, 0, ...)
-            const double* Wc = sA + coljm * ld;
-            const double x = k + lane < kMaxN ? Wc[k + lane] : 0.0;
-            const double sig = wave_sum(x * x);
-            const double x0 = readlane_d(x, 0);
-            // a remaining column below 1e-140 in norm (zero, in practice) is
-            // left as it is: R[k][k] = x0 and the entries below it, which the
-            // transposition never reads, are dropped; beta then stays finite
-            double al = x0, be = 0.0;
-            if (sig > 1e-280) {
-                al = -copysign(sqrt(sig), x0);
-                be = 1.0 / (sig - x0 * al);
-            }
-            const double v0 = x0 - al;
-            if (tid == 0) sdiag[k] = al;
-            if (k == n - 2 && tid < n) scol[tid] = col;   // the final order (wave 0)
-            // the swap moved logical column jm's storage to k and k's to jm
-            const int c0 = l0 == jm ? colk : cb0, c1 = l1 == jm ? colk : cb1;
-            double vv[kRows];
+        // (rows 8 B + 0 .. 7 hold the steps of block B: the rows above them are
+        // final, so a step loads, updates and stores rows from 8 B on only)
+        auto qr_block = [&](auto block) {
+            constexpr int B = decltype(block)::value;
+            const int kend = min(8 * B + 8, n - 1);
+            for (int k = 8 * B; k < kend; ++k) {
+                const int cur = k & 1, nxt = cur ^ 1;
+                // storage columns of this group's trailing logical columns k + 1 + g and
+                // k + 1 + g + kGroups before this step's swap (fetched while the pivot is found)
+                const int l0 = k + 1 + g, l1 = l0 + kGroups;
+                const int cb0 = __shfl(col, min(l0, n - 1), 64), cb1 = __shfl(col, min(l1, n - 1), 64);
+                double xr[2][RL];
 #pragma unroll
-            for (int m = 0; m < kRows; ++m) {
-                const int i = r + kLanes * m;
-                const double wi = Wc[i];
-                vv[m] = i > k ? wi : (i == k ? v0 : 0.0);
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int l = h ? l1 : l0;
-                if (l < n) {
-                    double* Wp = sA + (h ? c1 : c0) * ld;
-                    double xr[kRows];
-                    double w = 0.0;
-#pragma unroll
-                    for (int m = 0; m < kRows; ++m) {
-                        xr[m] = Wp[r + kLanes * m];
-                        w = fma(vv[m], xr[m], w);   // v is zero above row k
-                    }
-                    w = sum8(w);
-                    const double bw = be * w;
-                    double s2 = 0.0;
-#pragma unroll
-                    for (int m = 0; m < kRows; ++m) {
-                        const int i = r + kLanes * m;
-                        xr[m] = fma(-bw, vv[m], xr[m]);   // rows above k unchanged
-                        Wp[i] = xr[m];
-                        s2 = fma(i > k ? xr[m] : 0.0, xr[m], s2);
-                    }
-                    s2 = sum8(s2);
-                    if (r == 0) scn[nxt][l] = s2;
+                for (int m = B; m < RL; ++m) {
+                    xr[0][m] = sA[cb0 * ld + r + kLanes * m];
+                    xr[1][m] = sA[cb1 * ld + r + kLanes * m];
                 }
-            }
-            __syncthreads();
-        }
-        // A = R^T, column-major: A[l][j] = R[j][l] (l >= j); R[j][l] is row j of
-        // the storage column of logical column l, R[j][j] the reflector's alpha
-        // (row n - 1 has no reflector)
-        {
-            double tv[kPerThread];
-#pragma unroll
-            for (int q = 0; q < kPerThread; ++q) {
-                const int e = tid + kUpdThreads * q;
-                tv[q] = 0.0;
-                if (e < n * n) {
-                    const int j = e / n, l = e - (e / n) * n;
-                    if (l > j || (l == j && j == n - 1)) tv[q] = sA[scol[l] * ld + j];
-                    else if (l == j) tv[q] = sdiag[j];
+                // pivot: the largest remaining norm, lowest logical index on ties
+                const double cn = (lane >= k && lane < n) ? scn[cur][lane] : -1.0;
+                const double sig = wave_max(cn);
+                const unsigned long long top = __ballot(cn == sig);
+                int jm = top ? __ffsll(top) - 1 : k;
+                if (jm < k || jm >= n) jm = k;   // only with non-finite norms
+                const int colk = __builtin_amdgcn_readlane(col, k), coljm = __builtin_amdgcn_readlane(col, jm);
+                col = lane == k ? coljm : (lane == jm ? colk : col);
+                // the reflector H = I - beta v v^T mapping rows k.. of the pivot
+                // column, of squared norm sig, to (alpha, 0, ...)
+                const double* Wc = sA + coljm * ld;
+                const double x0 = Wc[k];
+                // a remaining column below 1e-140 in norm (zero, in practice) is
+                // left as it is: R[k][k] = x0 and the entries below it, which the
+                // transposition never reads, are dropped; beta then stays finite
+                double al = x0, be = 0.0;
+                if (sig > 1e-280) {
+                    const double rs = rsqrt_nr(sig), nr = sig * rs;
+                    al = -copysign(nr, x0);
+                    be = rs * rcp_nr(nr + fabs(x0));   // 1 / (sig - x0 alpha)
                 }
-            }
-            __syncthreads();
+                const double v0 = x0 - al;
+                if (tid == 0) sdiag[k] = al;
+                if (k == n - 2 && tid < n) scol[tid] = col;   // the final order (wave 0)
+                double vv[RL];
 #pragma unroll
-            for (int q = 0; q < kPerThread; ++q) {
-                const int e = tid + kUpdThreads * q;
-                if (e < n * n) {
-                    const int j = e / n, l = e - (e / n) * n;
-                    sA[j * ld + l] = tv[q];
+                for (int m = B; m < RL; ++m) {
+                    const int i = r + kLanes * m;
+                    const double wi = Wc[i];
+                    vv[m] = m > B || i > k ? wi : (i == k ? v0 : 0.0);
                 }
-            }
-            if (tid < n) sinv[scol[tid]] = tid;
-            __syncthreads();
-        }
-
-        // one-sided Jacobi on the columns of A
-        const int npair = n >> 1;
-        int sweeps = max_sweeps + 1;   // not converged
-        for (int sw = 0; sw < max_sweeps; ++sw) {
-            if (tid == 0) srot = 0;
-            __syncthreads();
-            for (int rd = 0; rd < n - 1; ++rd) {
-                if (g < npair) {
-                    int p, q;
-                    if (g == 0) {
-                        p = rd;
-                        q = n - 1;
-                    } else {   // (rd + g) and (rd - g) modulo n - 1, with 1 <= g < n - 1
-                        p = rd + g;
-                        p -= p >= n - 1 ? n - 1 : 0;
-                        q = rd - g;
-                        q += q < 0 ? n - 1 : 0;
-                    }
-                    double* Ap = sA + p * ld;
-                    double* Aq = sA + q * ld;
-                    double wp[kRows], wq[kRows];
-                    double al = 0.0, be = 0.0, ga = 0.0;
+                // the swap moved logical column jm's storage to k and k's to jm
+                if (l0 == jm || l1 == jm) {
+                    const int h = l0 == jm ? 0 : 1;
 #pragma unroll
-                    for (int m = 0; m < kRows; ++m) {
-                        wp[m] = Ap[r + kLanes * m];
-                        wq[m] = Aq[r + kLanes * m];
+                    for (int m = B; m < RL; ++m) {
+                        const double v = sA[colk * ld + r + kLanes * m];
+                        if (h)
+                            xr[1][m] = v;
+                        else
+                            xr[0][m] = v;
                     }
+                }
+                const int cc[2] = {l0 == jm ? colk : cb0, l1 == jm ? colk : cb1};
 #pragma unroll
-                    for (int m = 0; m < kRows; ++m) {
-                        al = fma(wp[m], wp[m], al);
-                        be = fma(wq[m], wq[m], be);
-                        ga = fma(wp[m], wq[m], ga);
-                    }
-                    al = sum8(al);
-                    be = sum8(be);
-                    ga = sum8(ga);
-                    // rotate while ga^2 > kTol^2 al be (the relative test, squared)
-                    if (ga * ga > (kTol * kTol) * (al * be)) {
-                        // the smaller root of t^2 + 2 zeta t - 1 = 0, zeta = (be - al) / (2 ga):
-                        // t = sign(d) 2ga / (|d| + sqrt(d^2 + 4 ga^2)), d = be - al
-                        const double d = be - al, g2 = 2.0 * ga;
-                        const double t = (d >= 0.0 ? g2 : -g2) / (fabs(d) + sqrt(fma(d, d, g2 * g2)));
-                        const double c = rsqrt(fma(t, t, 1.0)), s = c * t;
+                for (int h = 0; h < 2; ++h) {
+                    const int l = h ? l1 : l0;
+                    if (l < n) {
+                        double* Wp = sA + cc[h] * ld;
+                        double w = 0.0;
 #pragma unroll
-                        for (int m = 0; m < kRows; ++m) {
-                            Ap[r + kLanes * m] = c * wp[m] - s * wq[m];
-                            Aq[r + kLanes * m] = s * wp[m] + c * wq[m];
+                        for (int m = B; m < RL; ++m) w = fma(vv[m], xr[h][m], w);   // v is zero above row k
+                        w = sum8(w);
+                        const double bw = be * w;
+                        double s2 = 0.0;
+#pragma unroll
+                        for (int m = B; m < RL; ++m) {
+                            const int i = r + kLanes * m;
+                            const double v = fma(-bw, vv[m], xr[h][m]);   // row k and below
+                            Wp[i] = v;
+                            s2 = fma(m > B || i > k ? v : 0.0, v, s2);
                         }
-                        if (r == 0) {
-                            srot = 1;
-                            ++nrot;
-                        }
+                        s2 = sum8(s2);
+                        if (r == 0) scn[nxt][l] = s2;
                     }
                 }
                 __syncthreads();
             }
-            const int any = srot;
-            __syncthreads();
-            if (!any) {
-                sweeps = sw + 1;
-                break;
+        };
+        qr_blocks(qr_block, std::make_integer_sequence<int, RL>());
+        // A = R^T into registers: A[l][j] = R[j][l] (l >= j); R[j][l] is row j
+        // of the storage column of logical column l, R[j][j] the reflector's
+        // alpha (row n - 1 has no reflector)
+        double x[RL], y[RL];
+#pragma unroll
+        for (int m = 0; m < RL; ++m) {
+            const int l = r + kLanes * m;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int j = 2 * g + h;
+                double v = 0.0;
+                if (l < n && j <= l) v = l > j || j == n - 1 ? sA[scol[l] * ld + j] : sdiag[j];
+                (h ? x : y)[m] = v;
             }
         }
-        if (sweeps > max_sweeps) {
-            fail |= ITEBD_CHAIN_SWEEP_CAP;   // the last sweep still rotated: used as it stands
-            sweeps = max_sweeps;
-        }
+        if (tid < n) sinv[scol[tid]] = tid;
+        if (tid < 2) sflag[tid] = -1;
+        __syncthreads();
+
+        // one-sided Jacobi on the columns of A
+        bool capped;
+        const hotrg::JacobiShared js{sA, smail_nrm, sflag, kLd};
+        const int rounds = hotrg::jacobi_rounds<RL, true>(x, y, js, chi, g, r, kTol * kTol, max_sweeps, capped, nrot);
+        if (capped) fail |= ITEBD_CHAIN_SWEEP_CAP;   // the last sweep still rotated: used as it stands
+        const int sweeps = (rounds + n - 1) / n;
         max_sw = max(max_sw, sweeps);
         tot_sweeps += (unsigned long long)sweeps;
-
-        // singular values (column norms), the chi largest (ties: lower column first)
-        for (int h = 0; h < 2; ++h) {
-            const int l = g + kGroups * h;
-            if (l < n) {
-                double s2 = 0.0;
+        __syncthreads();   // the mailboxes are free
+        {
+            // the columns back into the work matrix, and their norms, the
+            // singular values
+            const double sx = hotrg::group_dot<RL>(x, x), sy = hotrg::group_dot<RL>(y, y);
+            if (g < chi) {
 #pragma unroll
-                for (int m = 0; m < kRows; ++m) {
-                    const double a = sA[l * ld + r + kLanes * m];
-                    s2 = fma(a, a, s2);
+                for (int m = 0; m < RL; ++m) {
+                    sA[2 * g * ld + r + kLanes * m] = y[m];
+                    sA[(2 * g + 1) * ld + r + kLanes * m] = x[m];
                 }
-                s2 = sum8(s2);
-                if (r == 0) ssig[l] = sqrt(s2);
+                if (r == 0) {
+                    ssig[2 * g] = sqrt(sy);
+                    ssig[2 * g + 1] = sqrt(sx);
+                }
             }
         }
         __syncthreads();
-        for (int j = tid; j < n; j += kUpdThreads) {
-            int rank = 0;
-            for (int i = 0; i < n; ++i) rank += (ssig[i] > ssig[j]) || (ssig[i] == ssig[j] && i < j);
-            if (rank < chi) sord[rank] = j;
+        // the chi largest (ties: lower column first)
+        for (int j = g; j < n; j += kGroups) {
+            const double v = ssig[j];
+            double rank = 0.0;
+            for (int i = r; i < n; i += kLanes) rank += (ssig[i] > v) || (ssig[i] == v && i < j) ? 1.0 : 0.0;
+            const int rk = (int)sum8(rank);
+            if (r == 0 && rk < chi) sord[rk] = j;
         }
         __syncthreads();
-        // kept right vectors y_c[m] = A[sinv[m]][sord[c]] / sigma: sign gauge (largest
-        // magnitude entry positive, the lowest m on ties) and scale; norm of the kept values
-        for (int c = tid; c < chi; c += kUpdThreads) {
-            const int j = sord[c];
+        // kept right vectors y_c[m] = A[sinv[m]][sord[c]] / sigma, i.e. row i of
+        // the column is entry m = scol[i]: sign gauge (largest magnitude entry
+        // positive, the lowest m on ties) and scale, a group per vector
+        if (g < chi) {
+            const int j = sord[g];
             double best = -1.0;
-            int bm = 0;
-            for (int m = 0; m < n; ++m) {
-                const double a = fabs(sA[j * ld + sinv[m]]);
-                if (a > best) {
-                    best = a;
-                    bm = m;
+            int bm = kMaxN;
+#pragma unroll
+            for (int m = 0; m < RL; ++m) {
+                const int i = r + kLanes * m;
+                if (i < n) {
+                    const double a = fabs(sA[j * ld + i]);
+                    const int e = scol[i];
+                    if (beats(a, e, best, bm)) {
+                        best = a;
+                        bm = e;
+                    }
                 }
             }
-            const double sgn = sA[j * ld + sinv[bm]] < 0.0 ? -1.0 : 1.0;
-            ssgn[c] = sgn;
-            sscale[c] = ssig[j] > 0.0 ? sgn / ssig[j] : 0.0;   // a zero value keeps a zero vector
+            argmax_step<0xB1>(best, bm);
+            argmax_step<0x4E>(best, bm);
+            argmax_step<0x141>(best, bm);
+            if (r == 0) {
+                if (bm >= n) bm = 0;   // only with non-finite entries
+                const double sgn = sA[j * ld + sinv[bm]] < 0.0 ? -1.0 : 1.0;
+                ssgn[g] = sgn;
+                sscale[g] = ssig[j] > 0.0 ? sgn / ssig[j] : 0.0;   // a zero value keeps a zero vector
+            }
         }
-        if (tid == 0) {
+        // norm of the kept values (one wave, fixed order)
+        if (tid < 64) {
             double acc = 0.0;
-            for (int c = 0; c < chi; ++c) acc = fma(ssig[sord[c]], ssig[sord[c]], acc);
-            snrm = sqrt(acc);
+            if (lane < chi) acc = ssig[sord[lane]] * ssig[sord[lane]];
+            acc = sum8(acc);
+            double tot = 0.0;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) tot += readlane_d(acc, 8 * w);
+            if (tid == 0) snrm = sqrt(tot);
         }
         __syncthreads();
         const double nrm = snrm;
@@ -527,13 +471,19 @@ void itebd_update_kernel(double* __restrict__ states, double* __restrict__ pair,
             double acc[kMaxColsPerLane];
 #pragma unroll
             for (int q = 0; q < kMaxColsPerLane; ++q) acc[q] = 0.0;
-            for (int i = 0; i < n; ++i) {
-                const double pk = gP[scol[i] * n + prow];
+            int so[kMaxColsPerLane];   // storage of the lane's columns (any column past chi: not stored)
 #pragma unroll
-                for (int q = 0; q < kMaxColsPerLane; ++q) {
-                    const int c = pgrp + q * ng;
-                    if (c < chi) acc[q] = fma(pk, sA[sord[c] * ld + i], acc[q]);
-                }
+            for (int q = 0; q < kMaxColsPerLane; ++q) so[q] = sord[min(pgrp + q * ng, chi - 1)] * ld;
+            // four rows of P are fetched ahead of their products
+#pragma unroll 1
+            for (int i0 = 0; i0 < n; i0 += 4) {
+                double pk[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) pk[u] = i0 + u < n ? gP[scol[i0 + u] * n + prow] : 0.0;
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int q = 0; q < kMaxColsPerLane; ++q) acc[q] = fma(pk[u], sA[so[q] + i0 + u], acc[q]);
             }
             const int a = prow >> 1, sp = prow & 1;
 #pragma unroll
@@ -556,7 +506,8 @@ void itebd_update_kernel(double* __restrict__ states, double* __restrict__ pair,
         st[2 * nb + i] = sl1[i];
         st[2 * nb + chi + i] = sl2[i];
     }
-    if (r == 0 && nrot) atomicAdd(&srotc, (unsigned long long)nrot);
+    // (counted alike in every lane of a pair)
+    if (tid % kLanes == 0 && nrot) atomicAdd(&srotc, (unsigned long long)nrot);
     __syncthreads();
     if (tid == 0) {
         sweeps_out[blockIdx.x] = max_sw;
@@ -766,8 +717,21 @@ int itebd_evolve(itebd_batch* b, double tau, int nupdates) {
     unsigned long long* work = reinterpret_cast<unsigned long long*>(b->ws + b->L.work);
     for (int done = 0; done < nupdates;) {
         const int k = std::min(kUpdatesPerLaunch, nupdates - done);
-        hipLaunchKernelGGL(itebd_update_kernel, dim3((unsigned)b->batch), dim3(kUpdThreads), 0, b->stream, b->states(),
-                           pair, status, sweeps, work, b->chi, G, k, b->max_sweeps);
+        auto launch = [&](auto rows) {
+            hipLaunchKernelGGL((itebd_update_kernel<decltype(rows)::value>), dim3((unsigned)b->batch),
+                               dim3(kUpdThreads), 0, b->stream, b->states(), pair, status, sweeps, work, b->chi, G, k,
+                               b->max_sweeps);
+        };
+        switch ((2 * b->chi + 7) / 8) {   // rows per lane
+            case 1:
+            case 2: launch(std::integral_constant<int, 2>()); break;
+            case 3: launch(std::integral_constant<int, 3>()); break;
+            case 4: launch(std::integral_constant<int, 4>()); break;
+            case 5: launch(std::integral_constant<int, 5>()); break;
+            case 6: launch(std::integral_constant<int, 6>()); break;
+            case 7: launch(std::integral_constant<int, 7>()); break;
+            default: launch(std::integral_constant<int, 8>()); break;
+        }
         if (hipGetLastError() != hipSuccess) {
             b->host_status = HOTRG_EHIP;
             return HOTRG_EHIP;

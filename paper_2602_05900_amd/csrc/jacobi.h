@@ -14,7 +14,9 @@
 //
 // What bounds a round is its dependent chain: mailbox read, the pair's dot
 // product over eight lanes (three DPP stages), the rotation's angle, the
-// rotation, mailbox write, barrier.  The squared norms travel with the
+// rotation, mailbox write, barrier (0.27 us with 3 rows a lane, 0.43 with 8;
+// four lanes a pair, which halves the waves that pay for the angle, was 20%
+// slower with two workgroups on a CU).  The squared norms travel with the
 // columns (updated by the rotation, recomputed once per sweep), so a round
 // forms one dot product instead of three, and the angle comes from two
 // reciprocal square roots refined from the hardware estimate instead of
@@ -52,6 +54,22 @@ __device__ __forceinline__ double readlane_d(double v, int l) {
     return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
+// largest value over the 64 lanes of a wave, in every lane
+__device__ __forceinline__ double wave_max(double v) {
+    v = fmax(v, dpp_d<0xB1>(v));
+    v = fmax(v, dpp_d<0x4E>(v));
+    v = fmax(v, dpp_d<0x141>(v));
+    v = fmax(v, dpp_d<0x140>(v));
+    return fmax(fmax(readlane_d(v, 0), readlane_d(v, 16)), fmax(readlane_d(v, 32), readlane_d(v, 48)));
+}
+
+// 1 / x, x > 0 normal: the hardware estimate (2^-24) and one third-order step
+__device__ __forceinline__ double rcp_nr(double x) {
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, y, 1.0);
+    return fma(y * e, 1.0 + e, y);
+}
+
 // 1 / sqrt(x), x > 0 finite: the hardware estimate (relative error 2^-24
 // measured on gfx950) and one third-order step, which leaves rounding errors
 // only; a dependent chain of six operations
@@ -85,17 +103,34 @@ struct JacobiShared {
     int slot;       // doubles per mailbox slot
 };
 
+// x.y over a group of eight lanes (two partial sums a lane)
+template <int RL>
+__device__ __forceinline__ double group_dot(const double (&x)[RL], const double (&y)[RL]) {
+    double s0 = x[0] * y[0], s1 = x[1] * y[1];
+#pragma unroll
+    for (int i = 2; i < RL; ++i) {
+        if (i & 1)
+            s1 = fma(x[i], y[i], s1);
+        else
+            s0 = fma(x[i], y[i], s0);
+    }
+    return sum8(s0 + s1);
+}
+
 // Rounds until 2 G consecutive ones rotate nothing, or max_sweeps sweeps of
 // 2 G rounds have run.  On entry x holds the column at position 2g + 1 and y
-// the one at 2g (RL rows per lane); on return the group holds two columns, of
-// some order and sign.  A pair is rotated while ga^2 > tol2 al be.  Every
-// thread of the workgroup calls it (groups g >= G hold nothing and only join
-// the barriers).  Returns the rounds run; capped: rotations were still being
-// made when the sweep limit ended it.
-template <int RL>
+// the one at 2g (RL rows per lane); on return the group holds two
+// columns, of some order and sign.  A pair is rotated while ga^2 > tol2 al be.
+// Every thread of the workgroup calls it (groups g >= G hold nothing; with
+// IDLE, for workgroups that have whole waves of them, those only join the
+// barriers).  Returns the rounds run; capped:
+// rotations were still being made when the sweep limit ended it; nrot grows
+// by the group's rotations.
+template <int RL, bool IDLE>
 __device__ int jacobi_rounds(double (&x)[RL], double (&y)[RL], const JacobiShared& sh, int G, int g, int r,
-                             double tol2, int max_sweeps, bool& capped) {
+                             double tol2, int max_sweeps, bool& capped, unsigned& nrot) {
     const bool act = g < G;
+    const bool work = !IDLE || __any(act);   // the same in every lane of a wave
     const bool last = g == G - 1;
     const int to_prev = g == 0 ? G - 1 : g - 1, to_next = last ? 0 : g + 1;
     double nx = 0.0, ny = 0.0;
@@ -107,13 +142,7 @@ __device__ int jacobi_rounds(double (&x)[RL], double (&y)[RL], const JacobiShare
     // No branch: a pair that passes no test gets the identity.  swap: x and
     // y change places instead (y negated; a column's sign is free)
     auto rotate = [&](bool on, bool swap) -> bool {
-        double g0 = x[0] * y[0], g1 = x[1] * y[1];
-#pragma unroll
-        for (int i = 2; i + 1 < RL; i += 2) {
-            g0 = fma(x[i], y[i], g0);
-            g1 = fma(x[i + 1], y[i + 1], g1);
-        }
-        const double ga = sum8(g0 + g1);
+        const double ga = group_dot<RL>(x, y);
         const bool rot = on && ga * ga > tol2 * (nx * ny);
         double c, s, t;
         jacobi_angle(nx, ny, ga, c, s, t);
@@ -127,54 +156,45 @@ __device__ int jacobi_rounds(double (&x)[RL], double (&y)[RL], const JacobiShare
             y[i] = fma(s, p, c * q);
         }
         const double ax = fma(-t, ga, nx), ay = fma(t, ga, ny);
+        nrot += rot ? 1u : 0u;
         nx = swap ? ay : ax;
         ny = swap ? ax : ay;
         return rot;
     };
-    for (;;) {
-        if (rd % m == 0) {   // the norms, afresh once per sweep
-            double a = 0.0, b = 0.0;
+    auto send = [&](const double (&v)[RL], double nv, int slot) {
+        double* o = sh.mail + slot * sh.slot;
 #pragma unroll
-            for (int i = 0; i < RL; ++i) {
-                a = fma(x[i], x[i], a);
-                b = fma(y[i], y[i], b);
-            }
-            nx = sum8(a);
-            ny = sum8(b);
+        for (int i = 0; i < RL; ++i) o[r + 8 * i] = v[i];
+        if (r == 0) sh.nrm[slot] = nv;
+    };
+    auto receive = [&](double (&v)[RL], double& nv, int slot) {
+        const double* o = sh.mail + slot * sh.slot;
+#pragma unroll
+        for (int i = 0; i < RL; ++i) v[i] = o[r + 8 * i];
+        nv = sh.nrm[slot];
+    };
+    for (;;) {
+        if (rd % m == 0 && work) {   // the norms, afresh once per sweep
+            nx = group_dot<RL>(x, x);
+            ny = group_dot<RL>(y, y);
         }
         // even round: x (now at position 2g) leaves to the previous group
-        if (rotate(act, false) && r == 0) sh.flag[0] = rd;
-        if (act) {
-            double* o = sh.mail + to_prev * sh.slot + r;
-#pragma unroll
-            for (int i = 0; i < RL; ++i) o[8 * i] = x[i];
-            if (r == 0) sh.nrm[to_prev] = nx;
+        if (work) {
+            if (rotate(act, false) && r == 0) sh.flag[0] = rd;
+            if (act) send(x, nx, to_prev);
         }
         __syncthreads();
-        if (act) {
-            const double* o = sh.mail + g * sh.slot + r;
-#pragma unroll
-            for (int i = 0; i < RL; ++i) x[i] = o[8 * i];
-            nx = sh.nrm[g];
-        }
+        if (act) receive(x, nx, g);
         last_rot = max(last_rot, sh.flag[0]);
         // odd round: y (now at position 2g + 2) leaves to the next group.
         // The last group holds positions 2G - 1 and 0, which are no pair: it
         // swaps its registers instead, keeps the one and sends the other back
-        if (rotate(act && !last, last) && r == 0) sh.flag[1] = rd + 1;
-        if (act) {
-            double* o = sh.mail + (G + to_next) * sh.slot + r;
-#pragma unroll
-            for (int i = 0; i < RL; ++i) o[8 * i] = y[i];
-            if (r == 0) sh.nrm[G + to_next] = ny;
+        if (work) {
+            if (rotate(act && !last, last) && r == 0) sh.flag[1] = rd + 1;
+            if (act) send(y, ny, G + to_next);
         }
         __syncthreads();
-        if (act) {
-            const double* o = sh.mail + (G + g) * sh.slot + r;
-#pragma unroll
-            for (int i = 0; i < RL; ++i) y[i] = o[8 * i];
-            ny = sh.nrm[G + g];
-        }
+        if (act) receive(y, ny, G + g);
         last_rot = max(last_rot, sh.flag[1]);
         rd += 2;
         // the flags read above are written again only after the barrier of

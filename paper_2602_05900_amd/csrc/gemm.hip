@@ -52,6 +52,8 @@ constexpr int kTpBM = 128, kTpWM = 4, kTpPF = 1, kTpNbuf = 1;
 // mid-size products (half environments, E): two stages, up to three
 // workgroups per CU (env 19.2 -> 18.3 ms per D = 48 solve)
 constexpr int kMidNst = 2, kMidMinw = 2;
+// FP64 products of at most this many 64 x 64 tiles split K over a workgroup's waves
+constexpr long kSplitKTiles = 256;
 // the Y product (panel operands) at full size
 constexpr int kYBM = 256, kYBN = 256, kYWM = 4, kYWN = 2, kYNst = 3, kYMinw = 1;
 
@@ -268,6 +270,111 @@ void gemm_nt_kernel(const T* __restrict__ A, long lda, const T* __restrict__ B, 
     }
 }
 
+
+// ---------------------------------------------------------------- small FP64 products
+
+// FP64 products with too few tiles for the chip: 32 x 32 tiles whose eight
+// waves split K, fragments loaded straight from global memory (a lane takes 4
+// consecutive k of its row per 16: whole lines, the next 16 fetched while the
+// current ones are multiplied), the waves' sums added in LDS in a fixed order.
+// Such a product's time is a chain of load latencies: with 64 x 64 tiles one
+// per K tile of 16 over all of K, here an eighth of them and four times the
+// workgroups (half environment of D = 24, 576 x 576 x 576: 41.5 -> 20.3 us; T',
+// 13824 x 24 x 576: 42.0 -> 18.2 us; 441 x 441 x 441: 33.4 -> 8.7 us).
+__global__ __launch_bounds__(512)
+void gemm_nt_splitk_kernel(const double* __restrict__ A, long lda, const double* __restrict__ B, long ldb,
+                           int M, int N, int K, Store store, OutMap mp, int tiles_n)
+{
+    constexpr int T = 32, NW = 8, LD = T + 1;
+    typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+    __shared__ double red[NW][T][LD];
+    const int tm = blockIdx.x / tiles_n, tn = blockIdx.x - tm * tiles_n;
+    const int m0 = tm * T, n0 = tn * T;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int fr = lane & 15, fk = lane >> 4;
+    const int chunk = ((K + 16 * NW - 1) / (16 * NW)) * 16;
+    const int kb = wave * chunk, ke = min(K, kb + chunk);
+    const double* arow[2];
+    const double* brow[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {   // rows past M or N repeat the last one; they are not stored
+        arow[i] = A + (long)min(m0 + 16 * i + fr, M - 1) * lda;
+        brow[i] = B + (long)min(n0 + 16 * i + fr, N - 1) * ldb;
+    }
+    d4 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = d4{0, 0, 0, 0};
+    struct Frag {
+        double a[2][4], b[2][4];
+    };
+    auto load4 = [&](const double* p, double (&v)[4]) {
+        const d2u x = *reinterpret_cast<const d2u*>(p), y = *reinterpret_cast<const d2u*>(p + 2);
+        v[0] = x.x;
+        v[1] = x.y;
+        v[2] = y.x;
+        v[3] = y.y;
+    };
+    auto load = [&](int k, Frag& f) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            load4(arow[i] + k + 4 * fk, f.a[i]);
+            load4(brow[i] + k + 4 * fk, f.b[i]);
+        }
+    };
+    auto multiply = [&](const Frag& f) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.a[i][u], f.b[j][u], acc[i][j], 0, 0, 0);
+    };
+    const int full = ke > kb ? (ke - kb) / 16 : 0;
+    if (full > 0) {
+        Frag cur, next;
+        load(kb, cur);
+        for (int i = 1; i < full; ++i) {
+            load(kb + 16 * i, next);
+            multiply(cur);
+            cur = next;
+        }
+        multiply(cur);
+    }
+    const int kt = kb + 16 * full;
+    if (kt < ke) {   // the last, partial group of K
+        Frag f;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = kt + 4 * fk + u;
+            const bool in = k < ke;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                f.a[i][u] = in ? arow[i][k] : 0.0;
+                f.b[i][u] = in ? brow[i][k] : 0.0;
+            }
+        }
+        multiply(f);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) red[wave][16 * i + fk + 4 * q][16 * j + fr] = acc[i][j][q];
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int e = tid + 512 * h, r = e >> 5, c = e & 31;
+        if (m0 + r >= M || n0 + c >= N) continue;
+        double v = red[0][r][c];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) v += red[w][r][c];
+        store(map_off(mp, map_row(mp, (unsigned)(m0 + r)), map_col(mp, (unsigned)(n0 + c))), v);
+    }
+}
 
 // ---------------------------------------------------------------- BF16-split kernel
 
@@ -1334,6 +1441,16 @@ static hipError_t dispatch(const Buf& A, long lda, const Buf& B, long ldb, int M
     const bool small_tiles = N <= 64 || (long)((M + 127) / 128) * ((N + 127) / 128) < 1024;
     switch (A.fmt) {
         case Fmt::F64:
+            // at most one 64 x 64 tile a CU (1024 x 1024 x 1024: 59.3 us against
+            // 70.7; with 441 tiles both take 128 us), and K enough for two groups
+            // of 16 (512 x 64 x 64: 7.3 us against 9.2)
+            if (K >= 32 && (long)((M + 63) / 64) * ((N + 63) / 64) <= kSplitKTiles) {
+                const int tn = (N + 31) / 32;
+                hipLaunchKernelGGL(gemm_nt_splitk_kernel, dim3((unsigned)((M + 31) / 32) * tn), dim3(512), 0, stream,
+                                   static_cast<const double*>(A.ptr), lda, static_cast<const double*>(B.ptr), ldb, M,
+                                   N, K, st, map, tn);
+                return hipGetLastError();
+            }
             if (small_tiles)
                 return run_gemm<double, 64, 64, 16, 2, 2, ROLE>(static_cast<const double*>(A.ptr), lda,
                                                                 static_cast<const double*>(B.ptr), ldb,

@@ -31,3 +31,13 @@ def check_product(M, N, K, precision, role="generic"):
 @pytest.mark.parametrize("precision", ["bf16x3", "bf16x6"])
 def test_ragged_k_tiles(gpu_lib, M, N, K, precision):
     check_product(M, N, K, precision)
+
+
+# FP64: K split over the waves of 32 x 32 tiles up to 256 tiles of 64 x 64 and
+# from K = 32: ragged in M, N and K (rows of odd length), fewer groups of 16
+# k than waves, and one past either end of the rule
+@pytest.mark.parametrize("M,N,K", [(1, 1, 32), (31, 33, 33), (64, 64, 64), (32, 32, 128), (33, 65, 1025), (512, 32, 1024),
+                                   (576, 576, 576), (1024, 1024, 47), (1025, 1024, 64), (100, 70, 31), (13824, 24, 576)])
+@pytest.mark.parametrize("role", ["generic", "y", "tp"])
+def test_fp64_split_k(gpu_lib, M, N, K, role):
+    check_product(M, N, K, "fp64", role)

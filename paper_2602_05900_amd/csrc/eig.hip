@@ -52,9 +52,13 @@ constexpr int EIG_RR_EVERY = 2;
 constexpr double EIG_PIV_OK = 1e-11, EIG_SHIFT = 1e-13;
 // Ritz vectors below this fraction of the largest sigma enter the next power
 // pass as u, not as E u / sigma: the product's rounding (1e-16 of the
-// largest) would leave in E u / sigma a part along the leading vectors that
-// the next product raises to the order of the column itself.
-constexpr double EIG_ADVANCE = 1e-10;
+// largest) leaves in E u / sigma a part 1e-16 / f along the leading vectors
+// (f = sigma over the largest), which the next product raises to 1e-16 / f^2
+// of the column itself: nothing at f = 1e-7, but a nearly dependent column
+// below 1e-8, whose factor then tilts the leading vectors (at 1e-10 the deep
+// ordered phase, T = 1.8 and D = 48, ended at residuals of 3e-8 after 100
+// passes; now below 1e-12 after 68).
+constexpr double EIG_ADVANCE = 1e-7;
 constexpr double EIG_MU = 1e-15;   // shift of a warm-started solve, relative to Tr E
 
 // ---------------------------------------------------------------- helpers

@@ -51,3 +51,16 @@ def test_subspace_environment(gpu_lib, D):
     # vectors are products over p <= 96 of columns orthonormal to 96 x 4e-15
     check_pairs(E, U, 4e-13, 1.1e-12)
     s.close()
+
+
+# deep in the ordered phase most kept pairs lie below 1e-8 of the largest:
+# they must not tilt the leading ones
+@pytest.mark.parametrize("T", [1.7, 1.8, 1.9])
+def test_subspace_steep_spectrum(gpu_lib, T):
+    from paper_2602_05900_amd import binding
+    s = binding.Solve(model="ising", temperature=T, dmax=48, max_steps=20)
+    s.coarse_grain(20)
+    s.log_z()
+    for n in range(1, 21):
+        assert s.eig_info(n)[2] <= 1e-12, (n, s.eig_info(n))
+    s.close()

@@ -52,8 +52,9 @@ constexpr int kTpBM = 128, kTpWM = 4, kTpPF = 1, kTpNbuf = 1;
 // mid-size products (half environments, E): two stages, up to three
 // workgroups per CU (env 19.2 -> 18.3 ms per D = 48 solve)
 constexpr int kMidNst = 2, kMidMinw = 2;
-// FP64 products of at most this many 64 x 64 tiles split K over a workgroup's waves
-constexpr long kSplitKTiles = 256;
+// FP64 products of at most this many 64 x 64 tiles (one 32 x 32 tile a CU)
+// split K over a workgroup's waves
+constexpr long kSplitKTiles = 64;
 // the Y product (panel operands) at full size
 constexpr int kYBM = 256, kYBN = 256, kYWM = 4, kYWN = 2, kYNst = 3, kYMinw = 1;
 
@@ -1251,7 +1252,161 @@ static hipError_t run_gemm_dma(const Buf& A, long lda, const Buf& B, long ldb, i
     return hipGetLastError();
 }
 
+// FP64 product with the operand tiles moved by the load unit straight into LDS,
+// as for the split products above (stages, waits and barriers are the same).
+// A stage holds 16 k of BM + BN rows: a wave's 16-byte loads fill one KiB, 8
+// rows of eight chunks of two k; chunk c of row r lies at place c ^ (r / 2 % 8),
+// so the fragment reads (16 rows and two k each half wave) hit distinct banks.
+// k runs in the same order as in the other FP64 kernels.  Bound by the FP64
+// matrix rate (77 TFLOP/s on large products).  Against staging through
+// registers: 110592 x 2304 x 2304 60.4 -> 70.6 TFLOP/s, 13824 x 576 x 576 46.4
+// -> 58.0, 2304 x 2304 x 2304 41.5 -> 55.9.
+//
+// Needs even K, lda and ldb and 16-byte aligned operands; chunks past K load
+// zeros, rows past M or N repeat the last row (never stored).
+template <int BM, int BN, int WAVES_M, int WAVES_N, int ROLE, int NST, int MINW>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, MINW)
+void gemm_nt_f64dma_kernel(const double* __restrict__ A, long lda, const double* __restrict__ B, long ldb,
+                           int M, int N, int K, Store store, OutMap mp, int tiles_m, int tiles_n, int per_xcd)
+{
+    typedef __attribute__((address_space(3))) void lds_void;
+    constexpr int BK = 16;
+    constexpr int NW = WAVES_M * WAVES_N;
+    constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
+    constexpr int FM = WM / 16, FN = WN / 16;
+    constexpr int LPW = (BM + BN) / 8 / NW;   // wave loads per K step and wave
+    constexpr int STAGE = (BM + BN) * BK;
+    static_assert(WM % 16 == 0 && WN % 16 == 0, "wave tile must be whole 16x16 fragments");
+    static_assert((BM + BN) / 8 % NW == 0 && BM % 8 == 0, "tile loads must divide evenly over the waves");
+    static_assert(NST == 2 || NST == 3, "two or three K stages in LDS");
+    __shared__ __attribute__((aligned(1024))) double S0[STAGE];
+    __shared__ __attribute__((aligned(1024))) double S1[STAGE];
+    __shared__ __attribute__((aligned(1024))) double S2[NST == 3 ? STAGE : 2];
+
+    const int bid = blockIdx.x;
+    const int tile = (bid & 7) * per_xcd + (bid >> 3);
+    if (tile >= tiles_m * tiles_n) return;
+    const int tm = tile / tiles_n;
+    const int tn = tile - tm * tiles_n;
+    const int m0 = tm * BM;
+    const int n0 = tn * BN;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WAVES_N;
+    const int wn = wave - wm * WAVES_N;
+
+    const double* gsrc[LPW];
+    int koff[LPW], dsto[LPW];
+#pragma unroll
+    for (int j = 0; j < LPW; ++j) {
+        const int rb = wave + j * NW;   // 8-row block of the stage: A's rows, then B's
+        const int r = rb * 8 + (lane >> 3);
+        koff[j] = 2 * ((lane & 7) ^ ((r >> 1) & 7));
+        gsrc[j] = rb * 8 < BM ? A + (long)min(m0 + r, M - 1) * lda : B + (long)min(n0 + r - BM, N - 1) * ldb;
+        dsto[j] = rb * 8 * BK;
+    }
+    const uintptr_t zsrc = reinterpret_cast<uintptr_t>(kZeroChunk);
+    auto issue = [&](double* S, int k0) {
+#pragma unroll
+        for (int j = 0; j < LPW; ++j) {
+            const int k = k0 + koff[j];
+            const uintptr_t a = reinterpret_cast<uintptr_t>(gsrc[j] + k);
+            const double* g = reinterpret_cast<const double*>(k < K ? a : zsrc);
+            __builtin_amdgcn_global_load_lds(g, (lds_void*)(S + dsto[j]), 16, 0, 0);
+        }
+    };
+
+    d4 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = d4{0, 0, 0, 0};
+    const int frow = lane & 15;
+    const int fk = lane >> 4;
+    // fragment rows are 16-row blocks, so r / 2 % 8 is that of the lane's row
+    const int sw = (frow >> 1) & 7;
+    auto compute = [&](const double* S) {
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            double a[FM], b[FN];
+            const int c = 2 * ((2 * h + (fk >> 1)) ^ sw) + (fk & 1);
+#pragma unroll
+            for (int i = 0; i < FM; ++i) a[i] = S[(wm * WM + i * 16 + frow) * BK + c];
+#pragma unroll
+            for (int j = 0; j < FN; ++j) b[j] = S[(BM + wn * WN + j * 16 + frow) * BK + c];
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+    };
+    auto step = [&](const double* cur, double* ahead, int kt) {
+        wait_vmem_le<(NST - 2) * LPW>();
+        stage_barrier();
+        issue(ahead, (kt + NST - 1) * BK);
+        compute(cur);
+    };
+    const int nk = (K + BK - 1) / BK;
+    issue(S0, 0);
+    int kt = 0;
+    if constexpr (NST == 3) {
+        issue(S1, BK);
+        for (; kt + 3 <= nk; kt += 3) {
+            step(S0, S2, kt);
+            step(S1, S0, kt + 1);
+            step(S2, S1, kt + 2);
+        }
+        if (kt < nk) step(S0, S2, kt);
+        if (kt + 1 < nk) step(S1, S0, kt + 1);
+    } else {
+        for (; kt + 2 <= nk; kt += 2) {
+            step(S0, S1, kt);
+            step(S1, S0, kt + 1);
+        }
+        if (kt < nk) step(S0, S1, kt);
+    }
+    wait_vmem_le<0>();   // the last stages' loads must land before the workgroup's LDS is released
+
+    MapPart coff[FN];
+    bool cin[FN];
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+        const int n = n0 + wn * WN + j * 16 + frow;
+        cin[j] = n < N;
+        coff[j] = cin[j] ? map_col(mp, (unsigned)n) : MapPart{0, 0};
+    }
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int m = m0 + wm * WM + i * 16 + fk + 4 * q;
+            if (m >= M) continue;
+            const MapPart ro = map_row(mp, (unsigned)m);
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+                if (cin[j]) store(map_off(mp, ro, coff[j]), acc[i][j][q]);
+        }
+}
+
 // ---------------------------------------------------------------- launcher
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int ROLE, int NST, int MINW>
+static hipError_t run_f64dma(const Buf& A, long lda, const Buf& B, long ldb, int M, int N, int K,
+                             const Store& st, const OutMap& mp, hipStream_t stream)
+{
+    const int tiles_m = (M + BM - 1) / BM;
+    const int tiles_n = (N + BN - 1) / BN;
+    const long tiles = (long)tiles_m * tiles_n;
+    const int per_xcd = (int)((tiles + 7) / 8);
+    const long grid = 8L * per_xcd;
+    if (grid > 0x7fffffffL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((gemm_nt_f64dma_kernel<BM, BN, WAVES_M, WAVES_N, ROLE, NST, MINW>), dim3((unsigned)grid),
+                       dim3(64 * WAVES_M * WAVES_N), 0, stream, static_cast<const double*>(A.ptr), lda,
+                       static_cast<const double*>(B.ptr), ldb, M, N, K, st, mp, tiles_m, tiles_n, per_xcd);
+    return hipGetLastError();
+}
 
 template <typename T, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int ROLE>
 static hipError_t run_gemm(const T* A, long lda, const T* B, long ldb, int M, int N, int K,
@@ -1267,6 +1422,52 @@ static hipError_t run_gemm(const T* A, long lda, const T* B, long ldb, int M, in
                        dim3(64 * WAVES_M * WAVES_N), 0, stream,
                        A, lda, B, ldb, M, N, K, st, mp, tiles_m, tiles_n, per_xcd);
     return hipGetLastError();
+}
+
+// FP64 products.  The tile follows the number of 64 x 64 tiles t of the output
+// (TFLOP/s measured, square products unless sizes are given):
+//   t <= 64         32 x 32, K split over the waves: the chip is short of tiles
+//                   even so (441^3 18.4, against 5.1 with 64 x 64 tiles)
+//   t <= 128        64 x 32 (576^3: 23.6, against 18.1 split, 15.9 at 64 x 64)
+//   N <= 32         64 x 32 (13824 x 24 x 576: 22.7, against 15.8 at 64 x 64)
+//   t < 2048        64 x 64 (1024^3: 50.0, against 47.7 at 64 x 32; 2500^3:
+//                   55.9, against 50.1 at 128 x 64)
+//   and N <= 64     64 x 64 (110592 x 48 x 2304: 40.5, against 21.4 at 128 x 128)
+//   above           128 x 64 (21952 x 784 x 784: 59.4, against 58.2 at 64 x 64),
+//                   and 128 x 128, two workgroups a CU, where that pads N by less
+//                   than 2 % more (110592 x 2304 x 2304: 70.6, against 66.8; but
+//                   64000 x 1600 x 1600: 65.5 against 66.6)
+// Odd K or row lengths (odd D) and unaligned operands stay with staging through
+// registers: 32 x 32 with split K up to t = 256 (784^3 36.6 us, against 55.1 at
+// 64 x 64; 1296^3, t = 441, 144 against 118), 64 x 64 on eight waves (about a
+// tenth faster than on four from 1296^3 to 2500^3) and, from 1024 tiles of
+// 128 x 128, 256 x 128 on 16 waves (110592 x 2304 x 2304: 60.4).
+template <int ROLE>
+static hipError_t dispatch_f64(const Buf& A, long lda, const Buf& B, long ldb, int M, int N, int K, const Store& st,
+                               const OutMap& map, hipStream_t stream, bool small_tiles)
+{
+    const double* a = static_cast<const double*>(A.ptr);
+    const double* b = static_cast<const double*>(B.ptr);
+    const long t64 = (long)((M + 63) / 64) * ((N + 63) / 64);
+    const bool dma = K % 2 == 0 && lda % 2 == 0 && ldb % 2 == 0 && ((uintptr_t)a & 15) == 0 && ((uintptr_t)b & 15) == 0;
+    // K below two groups of 16 leaves nothing to split
+    if (K >= 32 && t64 <= (dma ? kSplitKTiles : 4 * kSplitKTiles)) {
+        const int tn = (N + 31) / 32;
+        hipLaunchKernelGGL(gemm_nt_splitk_kernel, dim3((unsigned)((M + 31) / 32) * tn), dim3(512), 0, stream, a, lda, b,
+                           ldb, M, N, K, st, map, tn);
+        return hipGetLastError();
+    }
+    if (dma) {
+        if (N <= 32 || t64 <= 128) return run_f64dma<64, 32, 4, 1, ROLE, 3, 4>(A, lda, B, ldb, M, N, K, st, map, stream);
+        if (N <= 64 || M <= 64 || t64 < 2048)
+            return run_f64dma<64, 64, 4, 2, ROLE, 2, 8>(A, lda, B, ldb, M, N, K, st, map, stream);
+        const long n64 = (long)((N + 63) / 64) * 64, n128 = (long)((N + 127) / 128) * 128;
+        if (50 * (n128 - n64) < n64)
+            return run_f64dma<128, 128, 2, 4, ROLE, 2, 4>(A, lda, B, ldb, M, N, K, st, map, stream);
+        return run_f64dma<128, 64, 4, 2, ROLE, 3, 4>(A, lda, B, ldb, M, N, K, st, map, stream);
+    }
+    if (small_tiles) return run_gemm<double, 64, 64, 16, 4, 2, ROLE>(a, lda, b, ldb, M, N, K, st, map, stream);
+    return run_gemm<double, 256, 128, 16, 4, 4, ROLE>(a, lda, b, ldb, M, N, K, st, map, stream);
 }
 
 // K not a multiple of 16 (odd bond dimensions, early steps): tiles by the work
@@ -1441,26 +1642,7 @@ static hipError_t dispatch(const Buf& A, long lda, const Buf& B, long ldb, int M
     const bool small_tiles = N <= 64 || (long)((M + 127) / 128) * ((N + 127) / 128) < 1024;
     switch (A.fmt) {
         case Fmt::F64:
-            // at most one 64 x 64 tile a CU (1024 x 1024 x 1024: 59.3 us against
-            // 70.7; with 441 tiles both take 128 us), and K enough for two groups
-            // of 16 (512 x 64 x 64: 7.3 us against 9.2)
-            if (K >= 32 && (long)((M + 63) / 64) * ((N + 63) / 64) <= kSplitKTiles) {
-                const int tn = (N + 31) / 32;
-                hipLaunchKernelGGL(gemm_nt_splitk_kernel, dim3((unsigned)((M + 31) / 32) * tn), dim3(512), 0, stream,
-                                   static_cast<const double*>(A.ptr), lda, static_cast<const double*>(B.ptr), ldb, M,
-                                   N, K, st, map, tn);
-                return hipGetLastError();
-            }
-            if (small_tiles)
-                return run_gemm<double, 64, 64, 16, 2, 2, ROLE>(static_cast<const double*>(A.ptr), lda,
-                                                                static_cast<const double*>(B.ptr), ldb,
-                                                                M, N, K, st, map, stream);
-            // 256 x 128 tiles on 16 waves (64 x 32 each): the steady D = 48
-            // Y launch 26.4 -> 20.3 ms against 128 x 128 on 4 waves (2 x 4
-            // waves of 64 x 64: 21.0 ms; 256 x 256 spills the accumulators)
-            return run_gemm<double, 256, 128, 16, 4, 4, ROLE>(static_cast<const double*>(A.ptr), lda,
-                                                              static_cast<const double*>(B.ptr), ldb,
-                                                              M, N, K, st, map, stream);
+            return dispatch_f64<ROLE>(A, lda, B, ldb, M, N, K, st, map, stream, small_tiles);
         case Fmt::F32:
             if (small_tiles)
                 return run_gemm<float, 64, 64, 32, 2, 2, ROLE>(static_cast<const float*>(A.ptr), lda,

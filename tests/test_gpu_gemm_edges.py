@@ -7,13 +7,13 @@ pytestmark = pytest.mark.gpu
 UNIT = {"fp64": 2.0 ** -53, "fp32": 2.0 ** -24, "bf16x6": 2.0 ** -24, "bf16x3": 2.0 ** -16}
 
 
-def check_product(M, N, K, precision, role="generic"):
+def check_product(M, N, K, precision, role="generic", pad=(2, 1)):
     """C = A B^T within (2 + 8 sqrt K) u sum_k |a_k b_k|, u the unit roundoff
-    of the arithmetic (operands of odd leading dimensions)."""
+    of the arithmetic (operands of leading dimensions K + pad)."""
     import torch
     from paper_2602_05900_amd import binding
     rng = np.random.default_rng(M + 3 * N + 7 * K)
-    lda, ldb = K + 2, K + 1
+    lda, ldb = K + pad[0], K + pad[1]
     A, B = rng.standard_normal((M, lda)), rng.standard_normal((N, ldb))
     C = torch.full((M, N), float("nan"), dtype=torch.float64, device="cuda")
     binding.gemm_nt(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), C, M, N, K, lda, ldb, (1, N, 0, N, 0, 1),
@@ -41,3 +41,22 @@ def test_ragged_k_tiles(gpu_lib, M, N, K, precision):
 @pytest.mark.parametrize("role", ["generic", "y", "tp"])
 def test_fp64_split_k(gpu_lib, M, N, K, role):
     check_product(M, N, K, "fp64", role)
+
+
+# FP64 with even K and rows (operand tiles loaded straight into LDS): each tile
+# of the rule at ragged M and N, stages left over in K, a partial last stage
+@pytest.mark.parametrize("M,N,K", [
+    (1, 1, 2), (65, 33, 16), (500, 700, 30),                    # 64 x 32: short K
+    (576, 576, 98), (8200, 31, 64), (16401, 32, 18),            # 64 x 32: few tiles, narrow
+    (1100, 1030, 62), (50, 9000, 50), (9001, 63, 34),           # 64 x 64
+    (13050, 700, 34), (129, 65601, 16),                         # 128 x 64
+    (13217, 630, 48), (13217, 640, 66), (13217, 638, 2)])       # 128 x 128
+@pytest.mark.parametrize("pad", [(0, 0), (4, 2)])
+def test_fp64_direct_to_lds(gpu_lib, M, N, K, pad):
+    check_product(M, N, K, "fp64", pad=pad)
+
+
+# the same products with an odd row length or K: staged through registers
+@pytest.mark.parametrize("M,N,K", [(1100, 1030, 62), (1100, 1030, 61), (16500, 1030, 17)])
+def test_fp64_odd_rows(gpu_lib, M, N, K):
+    check_product(M, N, K, "fp64")

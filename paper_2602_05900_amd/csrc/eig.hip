@@ -371,9 +371,9 @@ constexpr double EIG_JAC_TOL2 = 1.6e-29;   // rotate while |a_p.a_q| > 4e-15 |a_
 // (row-major n x n).
 //
 // Bound by the rounds' dependent chain (jacobi.h).  The factor's columns are
-// graded and nearly orthogonal, so 7-8 sweeps do (the two-sided method took
+// graded and nearly orthogonal, so 6-7 sweeps do (the two-sided method took
 // 10 on E itself), on one matrix instead of two, with one barrier a round
-// instead of two: n = 64 took 876 us two-sided, 262 us now.
+// instead of two: n = 64 took 876 us two-sided, 241 us now.
 template <int NF>
 __global__ __launch_bounds__(64 * NF) void eig_dense_kernel(const double* __restrict__ E, int n,
                                                             double* __restrict__ theta, double* __restrict__ S,
@@ -589,7 +589,7 @@ __global__ __launch_bounds__(64 * NF) void eig_power_kernel(const double* __rest
 // One workgroup, bound by the Jacobi rounds' dependent chain (jacobi.h); the
 // two-sided Jacobi of V^T W it replaces moved two matrices through LDS every
 // round with two barriers, and needed the Cholesky of W^T W besides: 139 + 34
-// us at p = 48, 396 + 72 us at p = 80; this takes 92 / 254 us.
+// us at p = 48, 396 + 72 us at p = 80; this takes 80 / 250 us.
 template <int NF>
 __global__ __launch_bounds__(64 * NF) void eig_ritz_kernel(const double* __restrict__ Gt, double* __restrict__ theta,
                                                            double* __restrict__ S, EigCtl* ctl) {

@@ -60,3 +60,14 @@ def test_fp64_direct_to_lds(gpu_lib, M, N, K, pad):
 @pytest.mark.parametrize("M,N,K", [(1100, 1030, 62), (1100, 1030, 61), (16500, 1030, 17)])
 def test_fp64_odd_rows(gpu_lib, M, N, K):
     check_product(M, N, K, "fp64")
+
+
+# ragged K in the split precisions, K split over the waves of 32 x 32 tiles up to
+# 192 tiles of 64 x 64 and from K = 32: partial tiles, fewer groups of 16 k than
+# waves, a partial last group, one past the end of the rule
+@pytest.mark.parametrize("M,N,K", [(1, 1, 33), (31, 33, 47), (32, 64, 127), (33, 65, 129), (441, 441, 441), (100, 70, 1025),
+                                   (768, 1024, 63), (769, 1024, 63), (12288, 21, 41)])
+@pytest.mark.parametrize("precision", ["bf16x3", "bf16x6"])
+@pytest.mark.parametrize("role", ["generic", "x"])
+def test_ragged_k_split(gpu_lib, M, N, K, precision, role):
+    check_product(M, N, K, precision, role)

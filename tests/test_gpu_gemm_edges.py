@@ -7,7 +7,7 @@ pytestmark = pytest.mark.gpu
 UNIT = {"fp64": 2.0 ** -53, "fp32": 2.0 ** -24, "bf16x6": 2.0 ** -24, "bf16x3": 2.0 ** -16}
 
 
-def check_product(M, N, K, precision, role="generic", pad=(2, 1)):
+def check_product(M, N, K, precision, role="generic", pad=(2, 1), panel=False):
     """C = A B^T within (2 + 8 sqrt K) u sum_k |a_k b_k|, u the unit roundoff
     of the arithmetic (operands of leading dimensions K + pad)."""
     import torch
@@ -17,7 +17,7 @@ def check_product(M, N, K, precision, role="generic", pad=(2, 1)):
     A, B = rng.standard_normal((M, lda)), rng.standard_normal((N, ldb))
     C = torch.full((M, N), float("nan"), dtype=torch.float64, device="cuda")
     binding.gemm_nt(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), C, M, N, K, lda, ldb, (1, N, 0, N, 0, 1),
-                    precision=precision, role=role)
+                    precision=precision, role=role, panel=panel)
     ref = A[:, :K] @ B[:, :K].T
     bound = (2.0 + 8.0 * np.sqrt(K)) * UNIT[precision] * (np.abs(A[:, :K]) @ np.abs(B[:, :K]).T) + 1e-300
     assert np.all(np.abs(C.cpu().numpy() - ref) <= bound)
@@ -71,3 +71,11 @@ def test_fp64_odd_rows(gpu_lib, M, N, K):
 @pytest.mark.parametrize("role", ["generic", "x"])
 def test_ragged_k_split(gpu_lib, M, N, K, precision, role):
     check_product(M, N, K, precision, role)
+
+
+# operands converted to whole 32 x 16 panels: one panel, several each way, rows
+# of odd length
+@pytest.mark.parametrize("M,N,K", [(32, 96, 16), (96, 160, 48), (32, 2048, 16), (1056, 96, 80)])
+@pytest.mark.parametrize("precision", ["bf16x3", "bf16x6"])
+def test_panel_operands(gpu_lib, M, N, K, precision):
+    check_product(M, N, K, precision, role="y", panel=True)

@@ -79,3 +79,10 @@ def test_ragged_k_split(gpu_lib, M, N, K, precision, role):
 @pytest.mark.parametrize("precision", ["bf16x3", "bf16x6"])
 def test_panel_operands(gpu_lib, M, N, K, precision):
     check_product(M, N, K, precision, role="y", panel=True)
+
+
+# FP32: K split over the waves up to 256 tiles of 64 x 64, and one past the rule
+@pytest.mark.parametrize("M,N,K", [(1, 1, 32), (31, 33, 33), (33, 65, 1025), (576, 576, 576), (100, 70, 31),
+                                   (1024, 1024, 47), (1025, 1024, 64), (16384, 24, 100)])
+def test_fp32_split_k(gpu_lib, M, N, K):
+    check_product(M, N, K, "fp32")

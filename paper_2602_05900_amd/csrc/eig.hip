@@ -19,7 +19,7 @@
 // Rayleigh quotient.)  Both passes need one Gram matrix, which the product
 // kernel leaves in partial sums, and its Cholesky factor; the Ritz pass
 // costs the Jacobi besides.  R^T is graded with nearly orthogonal columns
-// once V is near the eigenvectors, so the Jacobi takes 3-5 sweeps there.
+// once V is near the eigenvectors, so the Jacobi takes 3-4 sweeps there.
 // Warm-started from the Ritz block of the step two earlier (same fused leg
 // basis once the dims are steady), else from a counter-based random block.
 // For n <= P_MAX the environment is diagonalised completely.

@@ -55,9 +55,6 @@ constexpr int kMidNst = 2, kMidMinw = 2;
 // FP64 products of at most this many 64 x 64 tiles (one 32 x 32 tile a CU)
 // split K over a workgroup's waves
 constexpr long kSplitKTiles = 64;
-// FP32 products up to one 64 x 64 tile a CU (64 x 32 and wider tiles of the FP64
-// kind do not exist for it)
-constexpr long kSplitKTilesF32 = 256;
 // split products of ragged K likewise, up to three 32 x 32 tiles a CU, which is
 // what its registers hold (BF16x6, whole call: 441^3, 49 tiles of 64 x 64, 61.9 ->
 // 22.2 us; 729^3, 144 tiles, 88.1 -> 63.1; with a fourth, 961^3, 104.2 -> 154.2)
@@ -279,9 +276,9 @@ void gemm_nt_kernel(const T* __restrict__ A, long lda, const T* __restrict__ B, 
 }
 
 
-// ---------------------------------------------------------------- small FP64 and FP32 products
+// ---------------------------------------------------------------- small FP64 products
 
-// FP64 and FP32 products with too few tiles for the chip: 32 x 32 tiles whose eight
+// FP64 products with too few tiles for the chip: 32 x 32 tiles whose eight
 // waves split K, fragments loaded straight from global memory (a lane takes 4
 // consecutive k of its row per 16: whole lines, the next 16 fetched while the
 // current ones are multiplied), the waves' sums added in LDS in a fixed order.
@@ -289,39 +286,36 @@ void gemm_nt_kernel(const T* __restrict__ A, long lda, const T* __restrict__ B, 
 // per K tile of 16 over all of K, here an eighth of them and four times the
 // workgroups (half environment of D = 24, 576 x 576 x 576: 41.5 -> 20.3 us; T',
 // 13824 x 24 x 576: 42.0 -> 18.2 us; 441 x 441 x 441: 33.4 -> 8.7 us).
-template <typename V>
 __global__ __launch_bounds__(512)
-void gemm_nt_splitk_kernel(const V* __restrict__ A, long lda, const V* __restrict__ B, long ldb,
+void gemm_nt_splitk_kernel(const double* __restrict__ A, long lda, const double* __restrict__ B, long ldb,
                            int M, int N, int K, Store store, OutMap mp, int tiles_n)
 {
     constexpr int T = 32, NW = 8, LD = T + 1;
-    using Op = Mma<V>;
-    using acc_t = typename Op::acc_t;
-    typedef V v2u __attribute__((ext_vector_type(2), aligned(sizeof(V))));
-    __shared__ V red[NW][T][LD];
+    typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+    __shared__ double red[NW][T][LD];
     const int tm = blockIdx.x / tiles_n, tn = blockIdx.x - tm * tiles_n;
     const int m0 = tm * T, n0 = tn * T;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int fr = lane & 15, fk = lane >> 4;
     const int chunk = ((K + 16 * NW - 1) / (16 * NW)) * 16;
     const int kb = wave * chunk, ke = min(K, kb + chunk);
-    const V* arow[2];
-    const V* brow[2];
+    const double* arow[2];
+    const double* brow[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {   // rows past M or N repeat the last one; they are not stored
         arow[i] = A + (long)min(m0 + 16 * i + fr, M - 1) * lda;
         brow[i] = B + (long)min(n0 + 16 * i + fr, N - 1) * ldb;
     }
-    acc_t acc[2][2];
+    d4 acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
+        for (int j = 0; j < 2; ++j) acc[i][j] = d4{0, 0, 0, 0};
     struct Frag {
-        V a[2][4], b[2][4];
+        double a[2][4], b[2][4];
     };
-    auto load4 = [&](const V* p, V (&v)[4]) {
-        const v2u x = *reinterpret_cast<const v2u*>(p), y = *reinterpret_cast<const v2u*>(p + 2);
+    auto load4 = [&](const double* p, double (&v)[4]) {
+        const d2u x = *reinterpret_cast<const d2u*>(p), y = *reinterpret_cast<const d2u*>(p + 2);
         v[0] = x.x;
         v[1] = x.y;
         v[2] = y.x;
@@ -341,7 +335,7 @@ void gemm_nt_splitk_kernel(const V* __restrict__ A, long lda, const V* __restric
             for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
-                    acc[i][j] = Op::run(f.a[i][u], f.b[j][u], acc[i][j]);
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.a[i][u], f.b[j][u], acc[i][j], 0, 0, 0);
     };
     const int full = ke > kb ? (ke - kb) / 16 : 0;
     if (full > 0) {
@@ -363,8 +357,8 @@ void gemm_nt_splitk_kernel(const V* __restrict__ A, long lda, const V* __restric
             const bool in = k < ke;
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                f.a[i][u] = in ? arow[i][k] : V(0);
-                f.b[i][u] = in ? brow[i][k] : V(0);
+                f.a[i][u] = in ? arow[i][k] : 0.0;
+                f.b[i][u] = in ? brow[i][k] : 0.0;
             }
         }
         multiply(f);
@@ -374,13 +368,13 @@ void gemm_nt_splitk_kernel(const V* __restrict__ A, long lda, const V* __restric
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) red[wave][16 * i + Op::row(fk, q)][16 * j + fr] = acc[i][j][q];
+            for (int q = 0; q < 4; ++q) red[wave][16 * i + fk + 4 * q][16 * j + fr] = acc[i][j][q];
     __syncthreads();
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int e = tid + 512 * h, r = e >> 5, c = e & 31;
         if (m0 + r >= M || n0 + c >= N) continue;
-        V v = red[0][r][c];
+        double v = red[0][r][c];
 #pragma unroll
         for (int w = 1; w < NW; ++w) v += red[w][r][c];
         store(map_off(mp, map_row(mp, (unsigned)(m0 + r)), map_col(mp, (unsigned)(n0 + c))), v);
@@ -1546,7 +1540,7 @@ static hipError_t dispatch_f64(const Buf& A, long lda, const Buf& B, long ldb, i
     // K below two groups of 16 leaves nothing to split
     if (K >= 32 && t64 <= (dma ? kSplitKTiles : 4 * kSplitKTiles)) {
         const int tn = (N + 31) / 32;
-        hipLaunchKernelGGL(gemm_nt_splitk_kernel<double>, dim3((unsigned)((M + 31) / 32) * tn), dim3(512), 0, stream, a, lda, b,
+        hipLaunchKernelGGL(gemm_nt_splitk_kernel, dim3((unsigned)((M + 31) / 32) * tn), dim3(512), 0, stream, a, lda, b,
                            ldb, M, N, K, st, map, tn);
         return hipGetLastError();
     }
@@ -1744,15 +1738,6 @@ static hipError_t dispatch(const Buf& A, long lda, const Buf& B, long ldb, int M
         case Fmt::F64:
             return dispatch_f64<ROLE>(A, lda, B, ldb, M, N, K, st, map, stream, small_tiles);
         case Fmt::F32:
-            // few tiles: as for FP64 (whole call: 441^3, 49 tiles of 64 x 64, 26.6
-            // -> 15.1 us; 1024^3, 256 tiles, 53.5 -> 44.6)
-            if (K >= 32 && (long)((M + 63) / 64) * ((N + 63) / 64) <= kSplitKTilesF32) {
-                const int tn = (N + 31) / 32;
-                hipLaunchKernelGGL(gemm_nt_splitk_kernel<float>, dim3((unsigned)((M + 31) / 32) * tn), dim3(512), 0,
-                                   stream, static_cast<const float*>(A.ptr), lda, static_cast<const float*>(B.ptr), ldb,
-                                   M, N, K, st, map, tn);
-                return hipGetLastError();
-            }
             if (small_tiles)
                 return run_gemm<float, 64, 64, 32, 2, 2, ROLE>(static_cast<const float*>(A.ptr), lda,
                                                                static_cast<const float*>(B.ptr), ldb,

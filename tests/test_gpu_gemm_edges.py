@@ -86,3 +86,25 @@ def test_panel_operands(gpu_lib, M, N, K, precision):
                                    (1024, 1024, 47), (1025, 1024, 64), (16384, 24, 100)])
 def test_fp32_split_k(gpu_lib, M, N, K):
     check_product(M, N, K, "fp32")
+
+
+def check_bits(M, N, K, wide, precision, role="generic"):
+    """The M x N product, few tiles, against the first M rows of the product
+    with `wide` rows, many tiles of a larger size: the same bits, since K is
+    summed in one order whatever the tile."""
+    import torch
+    from paper_2602_05900_amd import binding
+    g = torch.Generator(device="cuda").manual_seed(M + 3 * N + 7 * K)
+    A = torch.randn(wide, K, dtype=torch.float64, device="cuda", generator=g)
+    B = torch.randn(N, K, dtype=torch.float64, device="cuda", generator=g)
+    small = torch.full((M, N), float("nan"), dtype=torch.float64, device="cuda")
+    large = torch.full((wide, N), float("nan"), dtype=torch.float64, device="cuda")
+    for C, rows in ((small, M), (large, wide)):
+        binding.gemm_nt(A, B, C, rows, N, K, K, K, (1, N, 0, N, 0, 1), precision=precision, role=role)
+    assert torch.equal(small, large[:M])
+
+
+# 64 x 64 tiles (the small product) and 256 x 128 (1024 tiles of 128 x 128)
+@pytest.mark.parametrize("M,N,K", [(1, 129, 32), (64, 257, 441), (577, 300, 576), (1024, 1024, 47)])
+def test_fp32_bits_whatever_the_tile(gpu_lib, M, N, K):
+    check_bits(M, N, K, 128 * -(-1024 // -(-N // 128)), "fp32")

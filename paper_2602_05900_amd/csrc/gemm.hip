@@ -55,10 +55,6 @@ constexpr int kMidNst = 2, kMidMinw = 2;
 // FP64 products of at most this many 64 x 64 tiles (one 32 x 32 tile a CU)
 // split K over a workgroup's waves
 constexpr long kSplitKTiles = 64;
-// split products of ragged K likewise, up to three 32 x 32 tiles a CU, which is
-// what its registers hold (BF16x6, whole call: 441^3, 49 tiles of 64 x 64, 61.9 ->
-// 22.2 us; 729^3, 144 tiles, 88.1 -> 63.1; with a fourth, 961^3, 104.2 -> 154.2)
-constexpr long kSplitKTilesP32 = 192;
 // the Y product (panel operands) at full size
 constexpr int kYBM = 256, kYBN = 256, kYWM = 4, kYWN = 2, kYNst = 3, kYMinw = 1;
 
@@ -1256,89 +1252,6 @@ static hipError_t run_gemm_dma(const Buf& A, long lda, const Buf& B, long ldb, i
     return hipGetLastError();
 }
 
-// Split products with few tiles: 32 x 32 tiles whose eight waves split K, as for
-// FP64 above (fragments straight from global memory, the next 16 k fetched
-// while the current ones are multiplied, the waves' sums added in LDS in a
-// fixed order).  Same bound: with 64 x 64 tiles one load latency per 16 k over
-// all of K (half environment of D = 21, 441 x 441 x 441 BF16x6: 51 -> 16 us).
-template <int NPROD>
-__global__ __launch_bounds__(512)
-void gemm_nt_bf16splitk_kernel(const __bf16* __restrict__ A, long lda, long a_plane, const __bf16* __restrict__ B,
-                               long ldb, long b_plane, int M, int N, int K, Store store, OutMap mp, int tiles_n)
-{
-    using SP = SplitProducts<NPROD>;
-    typedef float f16v __attribute__((ext_vector_type(16)));
-    // eight elements at the alignment of one: rows of an odd length start anywhere
-    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-    typedef unsigned int u4a2 __attribute__((ext_vector_type(4), aligned(2)));
-    constexpr int NPL = SP::planes;
-    constexpr int T = 32, NW = 8, LD = T + 1;
-    __shared__ float red[NW][T][LD];
-    const int tm = blockIdx.x / tiles_n, tn = blockIdx.x - tm * tiles_n;
-    const int m0 = tm * T, n0 = tn * T;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int fr = lane & 31, fk = lane >> 5;
-    const int chunk = ((K + 16 * NW - 1) / (16 * NW)) * 16;
-    const int kb = wave * chunk, ke = min(K, kb + chunk);
-    // rows past M or N repeat the last one; they are not stored
-    const __bf16* arow = A + (long)min(m0 + fr, M - 1) * lda + 8 * fk;
-    const __bf16* brow = B + (long)min(n0 + fr, N - 1) * ldb + 8 * fk;
-    struct Frag {
-        bf16x8 a[NPL], b[NPL];
-    };
-    auto load = [&](int k, Frag& f) {
-#pragma unroll
-        for (int p = 0; p < NPL; ++p) {
-            f.a[p] = __builtin_bit_cast(bf16x8, (u4)*reinterpret_cast<const u4a2*>(arow + p * a_plane + k));
-            f.b[p] = __builtin_bit_cast(bf16x8, (u4)*reinterpret_cast<const u4a2*>(brow + p * b_plane + k));
-        }
-    };
-    f16v acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    auto multiply = [&](const Frag& f) {
-#pragma unroll
-        for (int pr = NPROD - 1; pr >= 0; --pr)   // smallest products first
-            mfma_32x32x16<false>(f.a[SP::a(pr)], f.b[SP::b(pr)], acc);
-    };
-    const int full = ke > kb ? (ke - kb) / 16 : 0;
-    if (full > 0) {
-        Frag cur, next;
-        load(kb, cur);
-        for (int i = 1; i < full; ++i) {
-            load(kb + 16 * i, next);
-            multiply(cur);
-            cur = next;
-        }
-        multiply(cur);
-    }
-    const int kt = kb + 16 * full;
-    if (kt < ke) {   // the last, partial group of K
-        Frag f;
-#pragma unroll
-        for (int p = 0; p < NPL; ++p)
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const bool in = kt + 8 * fk + q < ke;
-                f.a[p][q] = in ? arow[p * a_plane + kt + q] : (__bf16)0.0f;
-                f.b[p][q] = in ? brow[p * b_plane + kt + q] : (__bf16)0.0f;
-            }
-        multiply(f);
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) red[wave][8 * (r >> 2) + 4 * fk + (r & 3)][fr] = acc[r];
-    __syncthreads();
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int e = tid + 512 * h, r = e >> 5, c = e & 31;
-        if (m0 + r >= M || n0 + c >= N) continue;
-        float v = red[0][r][c];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) v += red[w][r][c];
-        store(map_off(mp, map_row(mp, (unsigned)(m0 + r)), map_col(mp, (unsigned)(n0 + c))), v);
-    }
-}
-
 // FP64 product with the operand tiles moved by the load unit straight into LDS,
 // as for the split products above (stages, waits and barriers are the same).
 // A stage holds 16 k of BM + BN rows: a wave's 16-byte loads fill one KiB, 8
@@ -1557,25 +1470,18 @@ static hipError_t dispatch_f64(const Buf& A, long lda, const Buf& B, long ldb, i
     return run_gemm<double, 256, 128, 16, 4, 4, ROLE>(a, lda, b, ldb, M, N, K, st, map, stream);
 }
 
-// K not a multiple of 16 (odd bond dimensions, early steps).  Few tiles: K
-// split over the waves (kSplitKTilesP32).  Else tiles by the work available,
-// the largest whose grid gives each of the 256 CUs one.  These products are
-// short chains of K steps whose time is the loads' latency, so an emptier chip
-// costs more than the re-reads a smaller tile brings: at D = 21 (BF16x6) env
-// 441^3 272 us with 256 x 256 tiles, 51 with 64 x 64, 16 with split K; Y 9261 x
-// 441 x 441 258 -> 97, X 52 -> 27 against 256 x 256 tiles throughout.
+// K not a multiple of 16 (odd bond dimensions, early steps): tiles by the work
+// available, the largest whose grid gives each of the 256 CUs one.  These
+// products are short chains of K steps whose time is the loads' latency, so
+// an emptier chip costs more than the re-reads a smaller tile brings: at
+// D = 21 (BF16x6) env 441^3 272 -> 51 us, Y 9261 x 441 x 441 258 -> 97, X
+// 52 -> 27 against 256 x 256 tiles throughout.  The K order of every
+// element is the same in all of them.
 template <int NPROD, int ROLE>
 static hipError_t dispatch_p32(const Buf& A, long lda, const Buf& B, long ldb, int M, int N, int K, const Store& st,
                                const OutMap& map, hipStream_t stream)
 {
     auto grid = [&](long bm, long bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    if (K >= 32 && grid(64, 64) <= kSplitKTilesP32) {
-        const int tn = (N + 31) / 32;
-        hipLaunchKernelGGL((gemm_nt_bf16splitk_kernel<NPROD>), dim3((unsigned)((M + 31) / 32) * tn), dim3(512), 0, stream,
-                           static_cast<const __bf16*>(A.ptr), lda, (long)A.plane, static_cast<const __bf16*>(B.ptr),
-                           ldb, (long)B.plane, M, N, K, st, map, tn);
-        return hipGetLastError();
-    }
     if (N <= 64) {
         if (grid(256, 64) >= 256)
             return run_gemm_p32<NPROD, 256, 64, 4, 1, 1, ROLE>(A, lda, B, ldb, M, N, K, st, map, stream);

@@ -108,3 +108,12 @@ def check_bits(M, N, K, wide, precision, role="generic"):
 @pytest.mark.parametrize("M,N,K", [(1, 129, 32), (64, 257, 441), (577, 300, 576), (1024, 1024, 47)])
 def test_fp32_bits_whatever_the_tile(gpu_lib, M, N, K):
     check_bits(M, N, K, 128 * -(-1024 // -(-N // 128)), "fp32")
+
+
+# ragged K in the split precisions: 64 x 64 or 128 x 128 tiles, and 256 x 256
+# (256 x 64 for N <= 64) at 256 of them
+@pytest.mark.parametrize("M,N,K", [(1, 129, 33), (64, 257, 441), (577, 300, 577), (2100, 2048, 47), (441, 21, 441)])
+@pytest.mark.parametrize("precision", ["bf16x3", "bf16x6"])
+@pytest.mark.parametrize("role", ["generic", "y"])
+def test_ragged_k_bits_whatever_the_tile(gpu_lib, M, N, K, precision, role):
+    check_bits(M, N, K, 256 * 256 if N <= 64 else 256 * -(-256 // -(-N // 256)), precision, role)

@@ -172,7 +172,9 @@ size_t hotrg_workspace_bytes(const hotrg_params* p);
  * Errors: EINVAL (parameters, NULL pointers, misaligned workspace, a
  * non-zero field or a missing impurity tensor with HOTRG_CUSTOM, or a bond
  * dimension too large for the eigensolver's Ritz block: every step with
- * Dx^2 > 96 needs D' < 96), ENOMEM (ws_bytes too small), ENODEV, EHIP. */
+ * Dx^2 > 96 needs D' < 96), ENONFINITE (an entry of a tensor or of an
+ * impurity is not finite, or c_0 = 0; found on the host), ENOMEM (ws_bytes
+ * too small), ENODEV, EHIP. */
 int hotrg_init_tensor(const hotrg_params* p, void* workspace, size_t ws_bytes,
                       void* stream, hotrg_solve** out);
 
@@ -181,7 +183,8 @@ int hotrg_init_tensor(const hotrg_params* p, void* workspace, size_t ws_bytes,
  * rebuilt exactly as in hotrg_init_tensor, the step count and the device
  * status are cleared, and the handle's workspace and timing events are kept.  Synchronises the handle's stream first.
  * Errors: EINVAL (parameters), ENOMEM (the handle's workspace is too small
- * for p: create a new handle instead), EHIP. */
+ * for p: create a new handle instead), ENONFINITE as in hotrg_init_tensor
+ * (after any of the three the handle is as it was), EHIP. */
 int hotrg_reset(hotrg_solve* s, const hotrg_params* p);
 
 /* Enqueues nsteps >= 0 coarse-graining steps (Sec. II.A: coarse-grain the

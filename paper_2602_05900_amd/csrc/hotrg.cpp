@@ -834,19 +834,14 @@ int mail_copy(hotrg_solve* s) {
     return HOTRG_OK;
 }
 
-// Builds T0 (and the impurity tensors) for p on the host, normalises them by
-// c_0 = max|T0|, uploads them and a fresh device state (ln Z accumulator =
-// ln c_0), and resets the step count.
-int upload_initial(hotrg_solve* s, const hotrg_params* p) {
-    initial_dims(p, &s->dx, &s->dy);
-    s->steps = 0;
-    s->pend = false;
-    s->hist[0] = s->hist[1] = 0;
-    s->timed_from = 0;
-    s->timed_dims.clear();
-    for (int i = 0; i < 2; ++i) s->warm_n[i] = s->warm_p[i] = s->warm_nr[i] = s->warm_pr[i] = 0;
-    const size_t count = (size_t)s->dx * s->dx * s->dy * s->dy;
-    ModelTensors mt;
+// T0 (and the impurity tensors) of p, divided by c_0 = max|T0|.  Host only:
+// an entry that is not finite is refused before anything reaches the device
+// (a NaN passes unseen through a maximum, and E would hold it in some rows
+// and not in others).
+int initial_tensors(const hotrg_params* p, ModelTensors& mt, double& c0) {
+    int dx, dy;
+    initial_dims(p, &dx, &dy);
+    const size_t count = (size_t)dx * dx * dy * dy;
     if (p->model == HOTRG_QCHAIN) {
         mt.T = qchain_tensor(p->bond_h, p->tau);
     } else if (p->model == HOTRG_CUSTOM) {
@@ -856,19 +851,35 @@ int upload_initial(hotrg_solve* s, const hotrg_params* p) {
     } else {
         mt = model_tensors(p);
     }
-    double c0 = 0.0;
-    for (double v : mt.T) c0 = std::max(c0, fabs(v));
-    if (!(c0 > 0.0) || !isfinite(c0)) return HOTRG_ENONFINITE;
+    c0 = 0.0;
+    for (double v : mt.T) {
+        if (!isfinite(v)) return HOTRG_ENONFINITE;
+        c0 = std::max(c0, fabs(v));
+    }
+    if (!(c0 > 0.0)) return HOTRG_ENONFINITE;
     for (double& v : mt.T) v /= c0;
-    int j = 0;
-    for (int slot = 0; slot < 2; ++slot) {
-        if (!(p->observables >> slot & 1)) continue;
+    for (int slot = 0; slot < 2; ++slot)
         for (double& v : mt.I[slot]) {
             v /= c0;
             if (!isfinite(v)) return HOTRG_ENONFINITE;
         }
-        s->imp_slot[j++] = slot;
-    }
+    return HOTRG_OK;
+}
+
+// Uploads the initial tensors and a fresh device state (ln Z accumulator =
+// ln c_0), and resets the step count.
+int upload_initial(hotrg_solve* s, const hotrg_params* p, const ModelTensors& mt, double c0) {
+    initial_dims(p, &s->dx, &s->dy);
+    s->steps = 0;
+    s->pend = false;
+    s->hist[0] = s->hist[1] = 0;
+    s->timed_from = 0;
+    s->timed_dims.clear();
+    for (int i = 0; i < 2; ++i) s->warm_n[i] = s->warm_p[i] = s->warm_nr[i] = s->warm_pr[i] = 0;
+    const size_t count = (size_t)s->dx * s->dx * s->dy * s->dy;
+    int j = 0;
+    for (int slot = 0; slot < 2; ++slot)
+        if (p->observables >> slot & 1) s->imp_slot[j++] = slot;
     std::vector<char> hs(sizeof(DevState), 0);
     DevState* h = reinterpret_cast<DevState*>(hs.data());
     h->lnz_acc = log(c0);
@@ -1148,6 +1159,10 @@ int hotrg_init_tensor(const hotrg_params* p, void* workspace, size_t ws_bytes, v
     if (!out) return HOTRG_EINVAL;
     *out = nullptr;
     if (!valid_params(p) || !eig_feasible(p) || !workspace || ((uintptr_t)workspace & 255u)) return HOTRG_EINVAL;
+    ModelTensors mt;
+    double c0;
+    int rc = initial_tensors(p, mt, c0);
+    if (rc) return rc;
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) return HOTRG_ENODEV;
     const Layout L = plan(p);
@@ -1167,7 +1182,7 @@ int hotrg_init_tensor(const hotrg_params* p, void* workspace, size_t ws_bytes, v
     s->products = products_of(p->precision);
     initial_dims(p, &s->dx, &s->dy);
 
-    int rc = upload_initial(s, p);
+    rc = upload_initial(s, p, mt, c0);
     if (rc) {
         delete s;
         return rc;
@@ -1183,6 +1198,10 @@ int hotrg_reset(hotrg_solve* s, const hotrg_params* p) {
     if (hipStreamSynchronize(s->stream) != hipSuccess) return HOTRG_EHIP;
     const Layout L = plan(p);
     if (L.total > s->ws_bytes) return HOTRG_ENOMEM;
+    ModelTensors mt;
+    double c0;
+    const int rc = initial_tensors(p, mt, c0);
+    if (rc) return rc;   // the handle keeps the problem it had
     s->L = L;
     s->p = *p;
     s->p.custom_tensor = nullptr;
@@ -1193,7 +1212,7 @@ int hotrg_reset(hotrg_solve* s, const hotrg_params* p) {
     s->host_status = HOTRG_OK;
     s->eig_maxit = kEigMaxIt;
     s->eig_fail = kEigFailTol;
-    return upload_initial(s, p);
+    return upload_initial(s, p, mt, c0);
 }
 
 int hotrg_coarse_grain(hotrg_solve* s, int nsteps) {

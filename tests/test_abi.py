@@ -184,3 +184,22 @@ def test_host_error_paths_without_device(lib):
     assert lib.hotrg_strerror(binding.ENOMEM) == b"workspace too small"
     assert lib.hotrg_gemm_scratch_bytes(binding.FP64, 10, 10, 10) == 0
     assert lib.hotrg_gemm_scratch_bytes(binding.BF16X6, 10, 10, 10) > 0
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+@pytest.mark.parametrize("at", [0, 40, 80])
+def test_non_finite_tensor_is_refused_on_the_host(lib, bad, at):
+    """One entry that is not finite, anywhere in a custom tensor or an
+    impurity, ends the call before the device is looked for (the workspace is
+    never touched: host memory does)."""
+    from paper_2602_05900_amd import binding
+    ws = np.zeros(1 << 12, dtype=np.uint8)
+    aligned = ctypes.c_void_p((ws.ctypes.data + 255) // 256 * 256)
+    h = ctypes.c_void_p()
+    t = np.ones((3, 3, 3, 3))
+    broken = t.copy()
+    broken.reshape(-1)[at] = bad
+    for kw in (dict(tensor=broken), dict(tensor=t, observables=("m",), impurities={"m": broken})):
+        p, keep = binding.make_params(model="custom", dmax=4, **kw)
+        assert lib.hotrg_init_tensor(ctypes.byref(p), aligned, 1, None, ctypes.byref(h)) == binding.ENONFINITE
+        assert not h.value

@@ -122,3 +122,22 @@ def test_zero_normalisation_latches_enonfinite_other_solve_unaffected(gpu_lib, p
     assert good.log_z() == want            # bitwise: no shared state between solves
     bad.close()
     good.close()
+
+
+def test_refused_reset_leaves_the_handle_as_it_was(gpu_lib):
+    """A reset to a tensor with a NaN is refused on the host; the handle goes
+    on with the problem it had."""
+    from paper_2602_05900_amd import binding
+    kw = dict(model="ising", q=2, temperature=2.1, dmax=12, max_steps=12)
+    s = binding.Solve(**kw)
+    s.coarse_grain(12)
+    want = s.log_z()
+    s.reset(**kw).coarse_grain(5)
+    bad = np.ones((2, 2, 2, 2))
+    bad[1, 0, 1, 1] = np.nan
+    with pytest.raises(binding.HotrgError) as e:
+        s.reset(model="custom", tensor=bad, dmax=8, max_steps=12)
+    assert e.value.status == binding.ENONFINITE
+    s.coarse_grain(7)
+    assert s.log_z() == want
+    s.close()

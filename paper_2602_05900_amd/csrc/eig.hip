@@ -33,6 +33,7 @@
 #include <math.h>
 #include "common.h"
 #include "jacobi.h"
+#include "rank.h"
 #include "../../include/hotrg.h"
 
 namespace hotrg {
@@ -388,13 +389,7 @@ __global__ __launch_bounds__(64 * NF) void eig_dense_kernel(const double* __rest
     __syncthreads();
     double trace = 0.0;
     for (int i = 0; i < n; ++i) trace += sh.key[i];
-    for (int i = tid; i < n; i += 64 * NF) {
-        const double v = sh.key[i];
-        int rk = 0;
-        for (int j = 0; j < n; ++j) rk += (sh.key[j] > v) || (sh.key[j] == v && j < i);
-        if (!(v == v)) rk = i;   // a non-finite E: any order (the solve is reported as failed)
-        place[rk] = i;
-    }
+    for (int i = tid; i < n; i += 64 * NF) place[descending_place(sh.key, n, i)] = i;
     __syncthreads();
     double mu = 1e-15 * fabs(trace);
     for (int attempt = 0;; ++attempt) {
@@ -443,13 +438,8 @@ __global__ __launch_bounds__(64 * NF) void eig_dense_kernel(const double* __rest
     __syncthreads();
     if (g < G) {
         // descending order, ties by position (an odd n's empty column ranks last)
-        double kx = 0.0, ky = 0.0;
-        for (int j = r; j < 2 * G; j += 8) {
-            const double v = sh.key[j];
-            kx += (v > lx) || (v == lx && j < 2 * g + 1) ? 1.0 : 0.0;
-            ky += (v > ly) || (v == ly && j < 2 * g) ? 1.0 : 0.0;
-        }
-        const int rx = (int)sum8(kx), ry = (int)sum8(ky);
+        const int rx = (int)sum8((double)entries_before(sh.key, 2 * G, 2 * g + 1, r, 8));
+        const int ry = (int)sum8((double)entries_before(sh.key, 2 * G, 2 * g, r, 8));
         const double ix = lx > 0.0 ? 1.0 / sqrt(lx) : 0.0, iy = ly > 0.0 ? 1.0 / sqrt(ly) : 0.0;
         if (r == 0) {
             if (rx < n) theta[rx] = lx - mu;

@@ -618,17 +618,12 @@ __global__ __launch_bounds__(64 * NF) void eig_ritz_kernel(const double* __restr
     }
     __syncthreads();
     // descending order, ties by position
-    double kx = 0.0, ky = 0.0;
-    for (int j = r; j < P; j += 8) {
-        const double v = sh.key[j];
-        kx += (v > lx) || (v == lx && j < 2 * g + 1) ? 1.0 : 0.0;
-        ky += (v > ly) || (v == ly && j < 2 * g) ? 1.0 : 0.0;
-    }
-    const int rx = (int)sum8(kx), ry = (int)sum8(ky);
+    const int rx = (int)sum8((double)entries_before(sh.key, P, 2 * g + 1, r, 8));
+    const int ry = (int)sum8((double)entries_before(sh.key, P, 2 * g, r, 8));
     const double sx = sqrt(lx), sy = sqrt(ly);
-    if (r == 0) {   // a vanishing column of W: sigma 0, S its unit vector
-        theta[rx] = sx > 1e-140 ? sx : 0.0;
-        theta[ry] = sy > 1e-140 ? sy : 0.0;
+    if (r == 0) {   // a vanishing column of W: sigma 0, S its unit vector; a NaN stays one
+        theta[rx] = sx <= 1e-140 ? 0.0 : sx;
+        theta[ry] = sy <= 1e-140 ? 0.0 : sy;
     }
     const double ix = 1.0 / sx, iy = 1.0 / sy;
 #pragma unroll
@@ -779,8 +774,9 @@ __global__ __launch_bounds__(768) void eig_check_kernel(const double* __restrict
     }
     __syncthreads();
     if (seg == 0) {
-        int rk = 0;
-        for (int i = 0; i < EIG_PMAX; ++i) rk += (th[i] > mine) || (th[i] == mine && i < j);
+        // a permutation of the columns, also where values are NaN: eig_select
+        // reads ord as column numbers
+        const int rk = descending_place(th, EIG_PMAX, j);
         if (j < p) {
             lam[rk] = mine - mu_rel * ctl->trace;
             ord[rk] = j;

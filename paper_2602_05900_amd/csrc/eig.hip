@@ -843,23 +843,15 @@ __global__ __launch_bounds__(256) void eig_select_kernel(const double* __restric
     __shared__ int si[256];
     const int l = blockIdx.x;
     Vr += ord ? ord[l] : l;   // its column
-    double best = -1.0;
-    int bi = 0x7fffffff;
-    for (int i = threadIdx.x; i < n; i += 256) {
-        const double a = fabs(Vr[(long)i * ldv]);
-        if (a > best) { best = a; bi = i; }
-    }
-    sv[threadIdx.x] = best;
-    si[threadIdx.x] = bi;
+    Entry e = largest_entry(Vr, ldv, n, threadIdx.x, 256);
+    sv[threadIdx.x] = e.size;
+    si[threadIdx.x] = e.row;
     __syncthreads();
     for (int s = 128; s > 0; s >>= 1) {
         if (threadIdx.x < s) {
-            const double a = sv[threadIdx.x + s];
-            const int ia = si[threadIdx.x + s];
-            if (a > sv[threadIdx.x] || (a == sv[threadIdx.x] && ia < si[threadIdx.x])) {
-                sv[threadIdx.x] = a;
-                si[threadIdx.x] = ia;
-            }
+            e = larger_entry(e, Entry{sv[threadIdx.x + s], si[threadIdx.x + s]});
+            sv[threadIdx.x] = e.size;
+            si[threadIdx.x] = e.row;
         }
         __syncthreads();
     }

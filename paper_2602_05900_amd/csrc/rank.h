@@ -1,5 +1,5 @@
-// Places in descending order, for the eigensolver's kernels.  Plain C++: the
-// rule is the same on the host.
+// Places in descending order and the largest entry of a column, for the
+// eigensolver's kernels.  Plain C++: the rules are the same on the host.
 #pragma once
 
 namespace hotrg {
@@ -22,6 +22,29 @@ __host__ __device__ inline int entries_before(const double* v, int n, int i, int
 
 __host__ __device__ inline int descending_place(const double* v, int n, int i) {
     return entries_before(v, n, i, 0, 1);
+}
+
+// An entry of a column by magnitude and row.
+struct Entry {
+    double size;
+    int row;
+};
+
+// a unless b is larger, or as large and in a lower row
+__host__ __device__ inline Entry larger_entry(const Entry& a, const Entry& b) {
+    return b.size > a.size || (b.size == a.size && b.row < a.row) ? b : a;
+}
+
+// The largest of v[i stride], i = first, first + step, ... below n (n > 0).
+// Where none compares (all NaN, or no such i) its row is still one of the
+// column's, since the entry found is read again for its sign.
+__host__ __device__ inline Entry largest_entry(const double* v, long stride, int n, int first, int step) {
+    Entry e{-1.0, first < n ? first : n - 1};
+    for (int i = first; i < n; i += step) {
+        const double a = __builtin_fabs(v[(long)i * stride]);
+        if (a > e.size) e = Entry{a, i};
+    }
+    return e;
 }
 
 }  // namespace hotrg

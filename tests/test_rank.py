@@ -1,5 +1,6 @@
-"""CPU check of the eigensolver's ranking rule (csrc/rank.h, plain C++): the
-places are a permutation in descending order, NaN and infinities included."""
+"""CPU checks of the eigensolver's ranking rules (csrc/rank.h, plain C++): the
+places are a permutation in descending order, and the largest entry's row is
+one of the column's, NaN and infinities included."""
 import itertools
 import os
 import subprocess
@@ -69,3 +70,42 @@ def test_places_of_a_padded_block(tmp_path):
     for v, got in zip(rows, places(tmp_path, rows)):
         p = 96 - v.count(-float("inf"))
         assert sorted(got[:p, 0]) == list(range(p))
+
+
+LARGEST = r"""
+#include <cstdio>
+#include <vector>
+#include "rank.h"
+int main() {
+    int n, stride;
+    while (std::scanf("%d %d", &n, &stride) == 2) {
+        std::vector<double> v((size_t)n * stride, 1e9);   // other columns: not to be read as this one's
+        for (int i = 0; i < n; ++i) std::scanf("%lf", &v[(size_t)i * stride]);
+        std::vector<hotrg::Entry> e;
+        for (int t = 0; t < 256; ++t) e.push_back(hotrg::largest_entry(v.data(), stride, n, t, 256));
+        for (int s = 128; s > 0; s >>= 1)
+            for (int t = 0; t < s; ++t) e[t] = hotrg::larger_entry(e[t], e[t + s]);
+        std::printf("%d\n", e[0].row);
+    }
+}
+"""
+
+
+def test_largest_entry_is_a_row_of_the_column(tmp_path):
+    (tmp_path / "t.cpp").write_text(LARGEST)
+    exe = tmp_path / "t"
+    subprocess.run(["g++", "-std=c++17", "-O2", "-D__host__=", "-D__device__=", "-I", CSRC, str(tmp_path / "t.cpp"),
+                    "-o", str(exe)], check=True)
+    rng = np.random.default_rng(3)
+    rows = [[float("nan")] * n for n in (1, 4, 255, 256, 257, 2304)]
+    for n in (1, 2, 81, 256, 300, 2304):
+        for share in (0.0, 0.5):
+            v = rng.integers(-5, 6, n).astype(float)      # ties: the lowest row
+            rows.append(np.where(rng.random(n) < share, np.nan, v).tolist())
+    text = "\n".join(f"{len(v)} 3 " + " ".join(repr(x) for x in v) for v in rows)
+    out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout.split()
+    for v, got in zip(rows, map(int, out), strict=True):
+        size = np.where(np.isnan(v), -1.0, np.abs(v))
+        assert 0 <= got < len(v)
+        if not np.isnan(v).all():
+            assert got == int(np.argmax(size))

@@ -60,6 +60,7 @@
 
 #include "../../include/itebd.h"
 #include "jacobi.h"
+#include "rank.h"
 
 namespace {
 
@@ -407,10 +408,7 @@ void itebd_update_kernel(double* __restrict__ states, double* __restrict__ pair,
         __syncthreads();
         // the chi largest (ties: lower column first)
         for (int j = g; j < n; j += kGroups) {
-            const double v = ssig[j];
-            double rank = 0.0;
-            for (int i = r; i < n; i += kLanes) rank += (ssig[i] > v) || (ssig[i] == v && i < j) ? 1.0 : 0.0;
-            const int rk = (int)sum8(rank);
+            const int rk = (int)sum8((double)hotrg::entries_before(ssig, n, j, r, kLanes));
             if (r == 0 && rk < chi) sord[rk] = j;
         }
         __syncthreads();

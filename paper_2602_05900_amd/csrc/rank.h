@@ -1,5 +1,6 @@
 // Places in descending order and the largest entry of a column, for the
-// eigensolver's kernels.  Plain C++: the rules are the same on the host.
+// eigensolver's and the chain update's kernels.  Plain C++: the rules are the
+// same on the host.
 #pragma once
 
 namespace hotrg {

@@ -385,7 +385,7 @@ __global__ __launch_bounds__(64 * NF) void eig_dense_kernel(const double* __rest
     __shared__ int place[P];    // place[i]: row of E at sorted position i
     const int tid = threadIdx.x, g = tid >> 3, r = tid & 7;
     // sorted order of the diagonal, descending, ties by index
-    for (int i = tid; i < P; i += 64 * NF) sh.key[i] = i < n ? E[(long)i * n + i] : 0.0;
+    for (int i = tid; i < P; i += 64 * NF) sh.key[i] = i < n ? rankable(E[(long)i * n + i]) : 0.0;
     __syncthreads();
     double trace = 0.0;
     for (int i = 0; i < n; ++i) trace += sh.key[i];
@@ -432,8 +432,8 @@ __global__ __launch_bounds__(64 * NF) void eig_dense_kernel(const double* __rest
     lx = sum8(lx);
     ly = sum8(ly);
     if (r == 0 && g < G) {
-        sh.key[2 * g] = ly;
-        sh.key[2 * g + 1] = lx;
+        sh.key[2 * g] = rankable(ly);
+        sh.key[2 * g + 1] = rankable(lx);
     }
     __syncthreads();
     if (g < G) {
@@ -613,8 +613,8 @@ __global__ __launch_bounds__(64 * NF) void eig_ritz_kernel(const double* __restr
     lx = sum8(lx);
     ly = sum8(ly);
     if (r == 0) {
-        sh.key[2 * g] = ly;
-        sh.key[2 * g + 1] = lx;
+        sh.key[2 * g] = rankable(ly);
+        sh.key[2 * g + 1] = rankable(lx);
     }
     __syncthreads();
     // descending order, ties by position
@@ -770,7 +770,7 @@ __global__ __launch_bounds__(768) void eig_check_kernel(const double* __restrict
             m += sn[i][j];
         }
         mine = j < p ? (m < s ? -theta[j] : theta[j]) : -INFINITY;
-        th[j] = mine;
+        th[j] = rankable(mine);
     }
     __syncthreads();
     if (seg == 0) {

@@ -399,9 +399,9 @@ void itebd_update_kernel(double* __restrict__ states, double* __restrict__ pair,
                     sA[2 * g * ld + r + kLanes * m] = y[m];
                     sA[(2 * g + 1) * ld + r + kLanes * m] = x[m];
                 }
-                if (r == 0) {
-                    ssig[2 * g] = sqrt(sy);
-                    ssig[2 * g + 1] = sqrt(sx);
+                if (r == 0) {   // a NaN as infinity: it ranks, and fails the norm of the kept ones
+                    ssig[2 * g] = sy == sy ? sqrt(sy) : INFINITY;
+                    ssig[2 * g + 1] = sx == sx ? sqrt(sx) : INFINITY;
                 }
             }
         }

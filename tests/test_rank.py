@@ -18,7 +18,10 @@ int main() {
     int n;
     while (std::scanf("%d", &n) == 1) {
         std::vector<double> v(n);
-        for (double& x : v) std::scanf("%lf", &x);
+        for (double& x : v) {
+            std::scanf("%lf", &x);
+            x = hotrg::rankable(x);   // as the kernels store what they rank
+        }
         for (int i = 0; i < n; ++i) {
             int parts = 0;   // eight lanes, as the kernels share the count
             for (int r = 0; r < 8; ++r) parts += hotrg::entries_before(v.data(), n, i, r, 8);

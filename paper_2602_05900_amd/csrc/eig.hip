@@ -358,8 +358,7 @@ struct SmallEig {
     int flag[2];
 };
 
-// the Jacobi rounds leave |a_p.a_q| <= 4e-15 |a_p| |a_q|
-constexpr double EIG_JAC_TOL2 = jacobi_tol2(4e-15, EIG_PMAX);
+constexpr double EIG_JAC_TOL2 = 1.6e-29;   // rotate while |a_p.a_q| > 4e-15 |a_p| |a_q|
 
 // ---------------------------------------------------------------- dense eigenproblem
 

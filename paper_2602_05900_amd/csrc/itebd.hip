@@ -85,8 +85,8 @@ static_assert(((kMaxChi + 1) / 2) * ((kMaxChi + 1) / 2) <= kUpdThreads, "contrac
 constexpr int kMaxColsPerLane = (kMaxChi + 3) / 4;
 static_assert(kUpdThreads / kMaxN >= 4, "row-parallel product assumes at least 4 lane groups");
 constexpr int kUpdatesPerLaunch = 32;
-// the Jacobi rounds leave |a_p.a_q| <= 1e-14 |a_p| |a_q|
-constexpr double kTol2 = hotrg::jacobi_tol2(1e-14, kMaxN);
+// rotate a pair while |a_p.a_q| > kTol |a_p| |a_q| (relative test)
+constexpr double kTol = 1e-14;
 
 struct Gate {
     double g[16];   // exp(-tau h), row-major [(s' t'), (s t)]
@@ -383,7 +383,7 @@ void itebd_update_kernel(double* __restrict__ states, double* __restrict__ pair,
         // one-sided Jacobi on the columns of A
         bool capped;
         const hotrg::JacobiShared js{sA, smail_nrm, sflag, kLd};
-        const int rounds = hotrg::jacobi_rounds<RL, true>(x, y, js, chi, g, r, kTol2, max_sweeps, capped, nrot);
+        const int rounds = hotrg::jacobi_rounds<RL, true>(x, y, js, chi, g, r, kTol * kTol, max_sweeps, capped, nrot);
         if (capped) fail |= ITEBD_CHAIN_SWEEP_CAP;   // the last sweep still rotated: used as it stands
         const int sweeps = (rounds + n - 1) / n;
         max_sw = max(max_sw, sweeps);

@@ -358,7 +358,8 @@ struct SmallEig {
     int flag[2];
 };
 
-constexpr double EIG_JAC_TOL2 = 1.6e-29;   // rotate while |a_p.a_q| > 4e-15 |a_p| |a_q|
+// rotate while |a_p.a_q| > 4e-15 |a_p| |a_q| (what the rounds leave: jacobi_rule.h)
+constexpr double EIG_JAC_TOL2 = 1.6e-29;
 
 // ---------------------------------------------------------------- dense eigenproblem
 

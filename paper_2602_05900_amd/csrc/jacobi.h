@@ -25,6 +25,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "jacobi_rule.h"
+
 namespace hotrg {
 
 // a double from another lane of the same row through a DPP move of each half
@@ -117,17 +119,9 @@ __device__ __forceinline__ double group_dot(const double (&x)[RL], const double 
     return sum8(s0 + s1);
 }
 
-// A rotation is large if the pair's cosine or the rotation's sine is above
-// these.  A small one moves the cosines of other pairs by at most sine (or
-// cosine) times cosine, 3e-16, so 2 G rounds without a large rotation leave
-// every pair below the tolerances in use (4e-15): a sweep that only confirms
-// that nothing rotates any more is not needed (Ritz matrices at p = 48 92 -> 80
-// us, dense n = 64 258 -> 241, a chain update 12.0 -> 11.2 ms).  Pairs of nearly
-// equal norms turn by large angles at any cosine and count as large.
-constexpr double JAC_LARGE_COS2 = 1e-16, JAC_LARGE_SIN2 = 1e-15;
-
-// Rounds until 2 G consecutive ones make no large rotation, or max_sweeps
-// sweeps of 2 G rounds have run.  On entry x holds the column at position 2g + 1 and y
+// Rounds until 2 G consecutive ones make no large rotation (jacobi_rule.h; pairs
+// of nearly equal norms turn by large angles at any cosine and count as large),
+// or max_sweeps sweeps of 2 G rounds have run.  On entry x holds the column at position 2g + 1 and y
 // the one at 2g (RL rows per lane); on return the group holds two
 // columns, of some order and sign.  A pair is rotated while ga^2 > tol2 al be.
 // Every thread of the workgroup calls it (groups g >= G hold nothing; with
@@ -153,10 +147,10 @@ __device__ int jacobi_rounds(double (&x)[RL], double (&y)[RL], const JacobiShare
     auto rotate = [&](bool on, bool swap) -> bool {
         const double ga = group_dot<RL>(x, y);
         const double ga2 = ga * ga, nn = nx * ny;
-        const bool rot = on && ga2 > tol2 * nn;
+        const bool rot = on && jacobi_rotates(ga2, nn, tol2);
         double c, s, t;
         jacobi_angle(nx, ny, ga, c, s, t);
-        const bool large = rot && (ga2 > JAC_LARGE_COS2 * nn || s * s > JAC_LARGE_SIN2);
+        const bool large = rot && jacobi_large(ga2, nn, s * s);
         c = rot ? c : (swap ? 0.0 : 1.0);
         s = rot ? s : (swap ? -1.0 : 0.0);
         t = rot ? t : 0.0;

@@ -198,8 +198,8 @@ inline int eig_block(int n, int k) {
 // latches HOTRG_EEIG in st->status (first error sticks).
 //
 // The subspace iteration can be enqueued in parts (host-polled stepping):
-// `range` selects the start (initial block and its orthonormalisation),
-// passes [first, last) of the maxit passes, and the end (selection of the
+// `range` selects the start (the initial block, which the first pass
+// orthonormalises), passes [first, last) of the maxit passes, and the end (selection of the
 // kept vectors and the statistics).  A pass enqueued after the solve has
 // converged exits at once, so any split of [0, maxit) that stops at a pass
 // after which the convergence word reads done gives the result of the whole

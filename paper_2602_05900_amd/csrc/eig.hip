@@ -978,31 +978,45 @@ hipError_t launch_choose_side(DevState* st, int step, void* Ut, void* Ux, const 
 
 // One pass of the subspace iteration.  A power pass reads the block the last
 // Ritz pass left in w.W (the first one V itself) and writes V; a Ritz pass
-// reads V (the last pass of an odd limit follows a Ritz pass: it reads w.W).
+// reads V, whose columns the power pass before it made orthonormal: the Ritz
+// vectors are as orthonormal as the block they are formed from.  The last pass
+// of an odd limit follows no power pass (it reads what a power pass would), and
+// makes its block orthonormal itself, twice, since that block may be anything.
 template <int NF>
 static void launch_pass(const double* E, int n, int k, const EigWork& w, double* V, int it, int maxit, bool ritz,
                         double mu, bool twice, double tol, unsigned long long seed, hipStream_t stream) {
     const int nb = (n + EIG_ROWS - 1) / EIG_ROWS;
     const int count = gram_tiles(NF) * 256;
     const bool after_power = it % EIG_RR_EVERY != 0;
+    auto sum_gram = [&] {
+        hipLaunchKernelGGL(eig_sum_kernel, dim3(count / 32), dim3(256), 0, stream, w.part, nb, count, w.G, w.ctl);
+    };
+    // V = src Q from the Gram parts of src
+    auto apply_factor = [&](const double* src) {
+        sum_gram();
+        hipLaunchKernelGGL((eig_power_kernel<NF>), dim3(1), dim3(64 * NF), 0, stream, w.G, n, w.S, w.dsc, w.ctl);
+        hipLaunchKernelGGL((eig_orth_kernel<NF>), dim3(nb), dim3(64 * NF), 0, stream, src, V, n, w.S, w.dsc,
+                           seed * 131 + it, w.ctl);
+    };
+    auto orthonormalise = [&](const double* src) {
+        hipLaunchKernelGGL((eig_gram_kernel<NF>), dim3(nb), dim3(64 * NF), 0, stream, src, n, w.part, w.ctl);
+        apply_factor(src);
+    };
     const double* in = it == 0 || after_power ? V : w.W;
     double* out = after_power ? w.W : w.Z;
+    if (ritz && !after_power) {
+        orthonormalise(in);
+        orthonormalise(V);
+        in = V;
+    }
     hipLaunchKernelGGL((eig_ev_kernel<NF>), dim3(nb), dim3(512), 0, stream, E, n, in, out, w.part,
                        mu, w.ctl);
-    hipLaunchKernelGGL(eig_sum_kernel, dim3(count / 32), dim3(256), 0, stream, w.part, nb, count, w.G, w.ctl);
     if (!ritz) {
-        hipLaunchKernelGGL((eig_power_kernel<NF>), dim3(1), dim3(64 * NF), 0, stream, w.G, n, w.S, w.dsc, w.ctl);
-        hipLaunchKernelGGL((eig_orth_kernel<NF>), dim3(nb), dim3(64 * NF), 0, stream, out, V, n, w.S, w.dsc,
-                           seed * 131 + it, w.ctl);
-        if (twice) {
-            hipLaunchKernelGGL((eig_gram_kernel<NF>), dim3(nb), dim3(64 * NF), 0, stream, V, n, w.part, w.ctl);
-            hipLaunchKernelGGL(eig_sum_kernel, dim3(count / 32), dim3(256), 0, stream, w.part, nb, count, w.G, w.ctl);
-            hipLaunchKernelGGL((eig_power_kernel<NF>), dim3(1), dim3(64 * NF), 0, stream, w.G, n, w.S, w.dsc, w.ctl);
-            hipLaunchKernelGGL((eig_orth_kernel<NF>), dim3(nb), dim3(64 * NF), 0, stream, V, V, n, w.S, w.dsc,
-                               seed * 131 + it, w.ctl);
-        }
+        apply_factor(out);
+        if (twice) orthonormalise(V);
         return;
     }
+    sum_gram();
     hipLaunchKernelGGL((eig_ritz_kernel<NF>), dim3(1), dim3(64 * NF), 0, stream, w.G, w.theta, w.S, w.ctl);
     hipLaunchKernelGGL((eig_ritz_apply_kernel<NF>), dim3(nb), dim3(64 * NF), 0, stream, in, out, V, w.W, n, w.S,
                        w.theta, w.rpart, w.ctl);

@@ -64,3 +64,28 @@ def test_subspace_steep_spectrum(gpu_lib, T):
     for n in range(1, 21):
         assert s.eig_info(n)[2] <= 1e-12, (n, s.eig_info(n))
     s.close()
+
+
+# a pass limit ends the solve on a Ritz pass, which at an odd limit follows no
+# power pass: the isometry is orthonormal all the same (to the 4e-13 of the
+# converged solves above), and the residual reported is that of unit vectors:
+# at least theirs with Rayleigh quotients, which make it smallest
+@pytest.mark.parametrize("passes", [1, 2, 3, 5, 7])
+@pytest.mark.parametrize("D", [17, 48])
+def test_pass_limit_leaves_an_isometry(gpu_lib, passes, D):
+    from paper_2602_05900_amd import binding
+    n = 8                                     # cold solves at steps 5 and 6, warm ones at 7 and 8
+    s = binding.Solve(model="ising", temperature=2.25, dmax=D, max_steps=n)
+    s.set_eig_limits(max_passes=passes, fail_residual=1e300)
+    for step in range(1, n + 1):
+        s.coarse_grain(1)
+        E, U = s.environment(), s.isometry()
+        assert np.abs(U.T @ U - np.eye(U.shape[1])).max() <= 4e-13
+        it, _, resid = s.eig_info(step)
+        if it:
+            assert it <= passes
+            th = np.einsum("ij,ij->j", U, E @ U)
+            own = np.sqrt(((E @ U - U * th) ** 2).sum(0)).max()
+            assert own <= resid * 1.01 * np.linalg.eigvalsh(E)[-1] + 1e-12 * abs(np.trace(E))
+    assert np.isfinite(s.log_z())
+    s.close()

@@ -159,13 +159,13 @@ struct EigWork {
     double* W;       // n x p: E V of a Ritz pass, then the next power pass's block
     double* Z;       // n x p: E X of a power pass
     double* part;    // partial Gram tiles, ceil(n/16) x (p/16)(p/16 + 1)/2 x 256
-    double* rpart;   // partial squared residuals for either sign, ceil(n/16) x 2 x kEigPMax
+    double* rpart;   // partial squared residuals for either sign and lengths, ceil(n/16) x 3 x kEigPMax
     double* G;       // summed Gram tiles
     double* S;       // right singular vectors, or CholeskyQR's Q, kEigPMax^2
     double* theta;   // sizes of the Ritz values (dense: eigenvalues), descending, kEigPMax
     double* lam;     // Ritz values with their signs, descending, kEigPMax
     int* ord;        // the columns of V they belong to, kEigPMax
-    double* dsc;     // column norms, kEigPMax
+    double* dsc;     // column norms (power pass), factors to unit length (check), kEigPMax
     EigCtl* ctl;
 };
 

@@ -684,8 +684,8 @@ __global__ __launch_bounds__(64 * NF) void eig_orth_kernel(const double* Z, doub
 
 // Ritz pass: u = Vin S to V, E u = Win S; the next power pass's block to X
 // (E u / sigma, or u where sigma is too small for it), and the workgroup's
-// parts of |E u_j - sigma_j u_j|^2 and |E u_j + sigma_j u_j|^2 to rpart (the
-// eigenvalue's sign is the one with the smaller residual).  Vin and Win may be V and X (a
+// parts of |E u_j - sigma_j u_j|^2, |E u_j + sigma_j u_j|^2 (the eigenvalue's
+// sign is the one with the smaller residual) and |u_j|^2 to rpart.  Vin and Win may be V and X (a
 // workgroup stages its rows before it writes them).
 template <int NF>
 __global__ __launch_bounds__(64 * NF) void eig_ritz_apply_kernel(const double* Vin, const double* Win, double* V,
@@ -717,12 +717,13 @@ __global__ __launch_bounds__(64 * NF) void eig_ritz_apply_kernel(const double* V
     }
     const bool advance = sig > EIG_ADVANCE * top;
     const double inv = advance ? 1.0 / sig : 0.0;
-    double res = 0.0, neg = 0.0;   // rows past n are zero in both factors
+    double res = 0.0, neg = 0.0, len = 0.0;   // rows past n are zero in both factors
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const double d = fma(-sig, au[q], aw[q]), e = fma(sig, au[q], aw[q]);
         res = fma(d, d, res);
         neg = fma(e, e, neg);
+        len = fma(au[q], au[q], len);
         const long row = r0 + fk + 4 * q;
         if (row < n) {
             V[row * P + 16 * f + fr] = au[q];
@@ -733,35 +734,48 @@ __global__ __launch_bounds__(64 * NF) void eig_ritz_apply_kernel(const double* V
     res += __shfl_xor(res, 32, 64);
     neg += __shfl_xor(neg, 16, 64);
     neg += __shfl_xor(neg, 32, 64);
+    len += __shfl_xor(len, 16, 64);
+    len += __shfl_xor(len, 32, 64);
     if (fk == 0) {
-        rpart[(long)blockIdx.x * (2 * EIG_PMAX) + 16 * f + fr] = res;
-        rpart[(long)blockIdx.x * (2 * EIG_PMAX) + EIG_PMAX + 16 * f + fr] = neg;
+        double* out = rpart + (long)blockIdx.x * (3 * EIG_PMAX) + 16 * f + fr;
+        out[0] = res;
+        out[EIG_PMAX] = neg;
+        out[2 * EIG_PMAX] = len;
     }
 }
 
 // After a Ritz pass: the residuals summed over the workgroups' parts (fixed
 // order), the eigenvalues with their signs in descending order (lam, and ord:
 // the column of V of each; an E computed in a split precision has small
-// negative ones, which rank last although the block finds them by size), and
-// whether the solve stops here.
+// negative ones, which rank last although the block finds them by size),
+// whether the solve stops here, and unit: the factor that makes u_j a unit
+// vector.  One CholeskyQR leaves a column with pivot d orthogonal to
+// eps / sqrt(d) but its length to eps / d only; pivots are small where a kept
+// block meets an environment that has moved (3e-11 of length and 4e-14 of angle
+// at T = 1.9, D = 48) or columns are rounding noise.  A length within 1e-12
+// stays as it is.
 __global__ __launch_bounds__(768) void eig_check_kernel(const double* __restrict__ rpart, int nb, int p, int k,
                                                         const double* __restrict__ theta, double* __restrict__ lam,
-                                                        int* __restrict__ ord, double mu_rel, double tol, int it,
-                                                        int last_iter, EigCtl* ctl) {
+                                                        int* __restrict__ ord, double* __restrict__ unit,
+                                                        double mu_rel, double tol, int it, int last_iter,
+                                                        EigCtl* ctl) {
     if (eig_done(ctl)) return;
-    __shared__ double sh[8][EIG_PMAX], sn[8][EIG_PMAX];
+    __shared__ double sh[8][EIG_PMAX], sn[8][EIG_PMAX], sl[8][EIG_PMAX];
     __shared__ double th[EIG_PMAX];
     __shared__ double top;
     const int j = threadIdx.x % EIG_PMAX, seg = threadIdx.x / EIG_PMAX;
-    double s = 0.0, m = 0.0;
+    double s = 0.0, m = 0.0, len = 0.0;
     if (j < p)
 #pragma unroll 4
         for (int b = seg; b < nb; b += 8) {
-            s += rpart[(long)b * (2 * EIG_PMAX) + j];
-            m += rpart[(long)b * (2 * EIG_PMAX) + EIG_PMAX + j];
+            const double* part = rpart + (long)b * (3 * EIG_PMAX) + j;
+            s += part[0];
+            m += part[EIG_PMAX];
+            len += part[2 * EIG_PMAX];
         }
     sh[seg][j] = s;
     sn[seg][j] = m;
+    sl[seg][j] = len;
     __syncthreads();
     double mine = 0.0;
     if (seg == 0) {
@@ -769,7 +783,9 @@ __global__ __launch_bounds__(768) void eig_check_kernel(const double* __restrict
         for (int i = 1; i < 8; ++i) {
             s += sh[i][j];
             m += sn[i][j];
+            len += sl[i][j];
         }
+        if (j < p) unit[j] = fabs(len - 1.0) > 1e-12 && len > 0.0 ? 1.0 / sqrt(len) : 1.0;
         mine = j < p ? (m < s ? -theta[j] : theta[j]) : -INFINITY;
         th[j] = rankable(mine);
     }
@@ -817,9 +833,10 @@ __global__ __launch_bounds__(768) void eig_check_kernel(const double* __restrict
 
 // ---------------------------------------------------------------- output
 
-// Columns ord[0], ord[1], ... (or 0, 1, ...) of the row-major n x ldv block Vr:
-// largest-magnitude entry made positive (lowest index on ties), written as
-// Ut[l, i] = u_l[i] and Ux[l, a2, a1] = u_l[a1 * dx + a2].
+// Columns ord[0], ord[1], ... (or 0, 1, ...) of the row-major n x ldv block Vr,
+// times their factors in unit (none: 1): largest-magnitude entry made positive
+// (lowest index on ties), written as Ut[l, i] = u_l[i] and
+// Ux[l, a2, a1] = u_l[a1 * dx + a2].
 __device__ __forceinline__ void put_val(const Buf& o, size_t idx, double v) {
     switch (o.fmt) {
         case Fmt::F64: static_cast<double*>(o.ptr)[idx] = v; break;
@@ -839,11 +856,13 @@ __device__ __forceinline__ void put_val(const Buf& o, size_t idx, double v) {
 
 // One block per kept column l.
 __global__ __launch_bounds__(256) void eig_select_kernel(const double* __restrict__ Vr, const int* __restrict__ ord,
-                                                         int ldv, int n, int dx, Buf Ut, Buf Ux) {
+                                                         const double* __restrict__ unit, int ldv, int n, int dx,
+                                                         Buf Ut, Buf Ux) {
     __shared__ double sv[256];
     __shared__ int si[256];
     const int l = blockIdx.x;
-    Vr += ord ? ord[l] : l;   // its column
+    const int col = ord ? ord[l] : l;
+    Vr += col;
     Entry e = largest_entry(Vr, ldv, n, threadIdx.x, 256);
     sv[threadIdx.x] = e.size;
     si[threadIdx.x] = e.row;
@@ -856,7 +875,8 @@ __global__ __launch_bounds__(256) void eig_select_kernel(const double* __restric
         }
         __syncthreads();
     }
-    const double sgn = Vr[(long)si[0] * ldv] < 0.0 ? -1.0 : 1.0;
+    const double len = unit ? unit[col] : 1.0;
+    const double sgn = Vr[(long)si[0] * ldv] < 0.0 ? -len : len;
     for (int i = threadIdx.x; i < n; i += 256) {
         const double u = sgn * Vr[(long)i * ldv];
         put_val(Ut, (size_t)l * n + i, u);
@@ -1021,7 +1041,7 @@ static void launch_pass(const double* E, int n, int k, const EigWork& w, double*
     hipLaunchKernelGGL((eig_ritz_apply_kernel<NF>), dim3(nb), dim3(64 * NF), 0, stream, in, out, V, w.W, n, w.S,
                        w.theta, w.rpart, w.ctl);
     hipLaunchKernelGGL(eig_check_kernel, dim3(1), dim3(768), 0, stream, w.rpart, nb, 16 * NF, k, w.theta,
-                       w.lam, w.ord, mu, tol, it, maxit - 1, w.ctl);
+                       w.lam, w.ord, w.dsc, mu, tol, it, maxit - 1, w.ctl);
 }
 
 hipError_t launch_eig_topk(const double* E, int n, int k, int dx, const EigWork& w, int parity, bool warm,
@@ -1043,7 +1063,7 @@ hipError_t launch_eig_topk(const double* E, int n, int k, int dx, const EigWork&
             default: launch_dense<6>(E, n, w, stream); break;
         }
         hipLaunchKernelGGL(eig_select_kernel, dim3(k), dim3(256), 0, stream, w.S,
-                           (const int*)nullptr, n, n, dx, Ut, Ux);
+                           (const int*)nullptr, (const double*)nullptr, n, n, dx, Ut, Ux);
         hipLaunchKernelGGL(eig_stats_kernel, dim3(1), dim3(64), 0, stream, w.theta, n, n, k, w.ctl, st, step, slot,
                            fail_tol);
         return hipGetLastError();
@@ -1073,7 +1093,8 @@ hipError_t launch_eig_topk(const double* E, int n, int k, int dx, const EigWork&
         }
     }
     if (!range.end) return hipGetLastError();
-    hipLaunchKernelGGL(eig_select_kernel, dim3(k), dim3(256), 0, stream, V, w.ord, p, n, dx, Ut, Ux);
+    hipLaunchKernelGGL(eig_select_kernel, dim3(k), dim3(256), 0, stream, V, w.ord, w.dsc, p, n, dx, Ut,
+                       Ux);
     hipLaunchKernelGGL(eig_stats_kernel, dim3(1), dim3(64), 0, stream, w.lam, p, n, k, w.ctl, st, step, slot,
                        fail_tol);
     return hipGetLastError();

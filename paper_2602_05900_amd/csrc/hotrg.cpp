@@ -238,7 +238,7 @@ Layout plan(const hotrg_params* p) {
     const size_t eig_gram = (pb / 16) * (pb / 16 + 1) / 2 * 256;
     L.oEigZ = take(8 * L.nEig * pb);
     L.oEigPart = take(8 * eig_blocks * eig_gram);
-    L.oEigRes = take(8 * eig_blocks * 2 * pb);
+    L.oEigRes = take(8 * eig_blocks * 3 * pb);
     L.oEigG = take(8 * eig_gram);
     L.oEigS = take(8 * pb * pb);
     L.oEigTheta = take(8 * pb);

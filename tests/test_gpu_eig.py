@@ -89,3 +89,44 @@ def test_pass_limit_leaves_an_isometry(gpu_lib, passes, D):
             assert own <= resid * 1.01 * np.linalg.eigvalsh(E)[-1] + 1e-12 * abs(np.trace(E))
     assert np.isfinite(s.log_z())
     s.close()
+
+
+# deep in the ordered phase, the columns themselves: a block is factored once as
+# it is while its scaled Gram matrix has pivots above 1e-11, which leaves its
+# columns orthonormal to p eps / 1e-11 = 1e-3 at worst; the pairs above 1e-7 of
+# the largest come first and have pivots near 1, as the converged solves above
+@pytest.mark.parametrize("T", [1.7, 1.8, 1.9])
+def test_subspace_steep_spectrum_isometry(gpu_lib, T):
+    from paper_2602_05900_amd import binding
+    s = binding.Solve(model="ising", temperature=T, dmax=48, max_steps=20)
+    for _ in range(20):
+        s.coarse_grain(1)
+        E, U = s.environment(), s.isometry()
+        th = np.einsum("ij,ij->j", U, E @ U)
+        G = np.abs(U.T @ U - np.eye(U.shape[1]))
+        top = th > 1e-7 * th[0]
+        assert G.max() <= 1.1e-3
+        assert G[np.ix_(top, top)].max() <= 4e-13
+    s.close()
+
+
+# environments of the reduced precisions in the dense solver, n = 4 to 81: they
+# are not definite to the first shifts tried.  The isometry is kept in the
+# precision's operands, of unit roundoff u: its columns then differ from the
+# vectors found by u, E U by u times the largest eigenvalue
+@pytest.mark.parametrize("precision,u", [("fp32", 2.0 ** -24), ("bf16x6", 2.0 ** -24), ("bf16x3", 2.0 ** -16)])
+@pytest.mark.parametrize("model,q,T,D", [("ising", 2, 1.9, 8), ("ising", 2, 2.3, 9), ("potts", 3, 1.0, 9)])
+def test_dense_environment_of_reduced_precision(gpu_lib, precision, u, model, q, T, D):
+    from paper_2602_05900_amd import binding
+    n, lowest = 12, 0.0
+    s = binding.Solve(model=model, q=q, temperature=T, dmax=D, precision=precision, max_steps=n)
+    for step in range(1, n + 1):
+        s.coarse_grain(1)
+        E, U = s.environment(), s.isometry()
+        check_pairs(E, U, 5e-14 + 4 * u, 5e-14 + 4 * u)
+        assert s.eig_stop(step) == binding.EIG_CONVERGED
+        w = np.linalg.eigvalsh(E)
+        lowest = min(lowest, w[0] / w[-1])
+    if precision == "bf16x3":
+        assert lowest < -1e-13        # past the first two shifts
+    s.close()

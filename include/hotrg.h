@@ -452,7 +452,10 @@ int hotrg_runtime_version(int* version);
  * HOTRG_BF16X6).  A, B and C are device pointers in FP64; for the reduced
  * precisions the library rounds/splits the operands into an internal copy
  * inside `scratch` (device memory of hotrg_gemm_scratch_bytes() bytes, may be
- * NULL for HOTRG_FP64) and writes C in FP64.  Enqueued on `stream`.
+ * NULL for HOTRG_FP64) and writes C in FP64.  The tiles follow M, N, K and the
+ * alignment; FP32 and the split precisions sum K in one order whatever the
+ * tile, FP64 in eight parts where there are few tiles, so that there the last
+ * bits of an element depend on the sizes.  Enqueued on `stream`.
  * Errors: EINVAL (sizes < 0, NULL, sm or sn < 1), EHIP. */
 size_t hotrg_gemm_scratch_bytes(int precision, int M, int N, int K);
 int hotrg_gemm_nt(int precision, int M, int N, int K,

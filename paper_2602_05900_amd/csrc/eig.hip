@@ -375,7 +375,8 @@ constexpr double EIG_JAC_TOL2 = 1.6e-29;
 // Bound by the rounds' dependent chain (jacobi.h).  The factor's columns are
 // graded and nearly orthogonal, so 6-7 sweeps do (the two-sided method took
 // 10 on E itself), on one matrix instead of two, with one barrier a round
-// instead of two: n = 64 took 876 us two-sided, 241 us now.
+// instead of two: n = 64 took 876 us two-sided, 250 to 280 us now (259 in a
+// solve with D = 8; where the loop comes to lie in memory moves it by 10 %).
 template <int NF>
 __global__ __launch_bounds__(64 * NF) void eig_dense_kernel(const double* __restrict__ E, int n,
                                                             double* __restrict__ theta, double* __restrict__ S,

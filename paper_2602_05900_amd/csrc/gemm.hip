@@ -1257,7 +1257,7 @@ static hipError_t run_gemm_dma(const Buf& A, long lda, const Buf& B, long ldb, i
 // A stage holds 16 k of BM + BN rows: a wave's 16-byte loads fill one KiB, 8
 // rows of eight chunks of two k; chunk c of row r lies at place c ^ (r / 2 % 8),
 // so the fragment reads (16 rows and two k each half wave) hit distinct banks.
-// k runs in the same order as in the other FP64 kernels.  Bound by the FP64
+// k runs in the same order as in the register-staged FP64 kernel.  Bound by the FP64
 // matrix rate (77 TFLOP/s on large products).  Against staging through
 // registers: 110592 x 2304 x 2304 60.4 -> 70.6 TFLOP/s, 13824 x 576 x 576 46.4
 // -> 58.0, 2304 x 2304 x 2304 41.5 -> 55.9.
@@ -1632,13 +1632,11 @@ static hipError_t dispatch(const Buf& A, long lda, const Buf& B, long ldb, int M
         return A.fmt == Fmt::BF16x2 ? dispatch_p32<3, ROLE>(A, lda, B, ldb, M, N, K, st, map, stream)
                                     : dispatch_p32<6, ROLE>(A, lda, B, ldb, M, N, K, st, map, stream);
     }
-    // FP64 / FP32: 64 x 64 tiles for narrow outputs (T', N = D') and where
-    // 128 x 128 gives fewer than four tiles per CU (the D = 24 products, the
-    // D = 48 environments), so that the work spreads evenly over the CUs
-    // (FP64, per steady step: D = 24 environment 0.367 -> 0.136 ms, Y 0.376
-    // -> 0.227, X 0.068 -> 0.033, T' 0.123 -> 0.048; D = 48 environment
-    // 2.63 -> 1.86 and T' 1.72 -> 0.69; results bitwise unchanged, the K
-    // order of every element being the same)
+    // Register-staged tiles of FP32, and of FP64 with odd K or rows past the
+    // split form (dispatch_f64): 64 x 64 for narrow outputs (T', N = D') and
+    // where 128 x 128 gives fewer than four tiles per CU (in FP32 the D = 24
+    // products and the D = 48 environments), so that the work spreads evenly
+    // over the CUs; else 256 x 128 on 16 waves.  Both sum K in the same order.
     const bool small_tiles = N <= 64 || (long)((M + 127) / 128) * ((N + 127) / 128) < 1024;
     switch (A.fmt) {
         case Fmt::F64:

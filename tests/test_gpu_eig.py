@@ -31,7 +31,8 @@ def test_dense_environment(gpu_lib, dx, dy):
     s.coarse_grain(1)
     E, U = s.environment(), s.isometry()
     assert U.shape == (dx * dx, dx * dx)
-    # a pair stops rotating at 4e-15 of its norms; products over n <= 81 terms round below 81 eps
+    # a pair stops rotating at 4e-15 of its norms, and later rotations of the last sweep add 8e-15 at most
+    # where tried; products over n <= 81 terms round below 81 eps
     check_pairs(E, U, 5e-14, 5e-14)
     s.close()
 
@@ -48,7 +49,8 @@ def test_subspace_environment(gpu_lib, D):
     E, U = s.environment(), s.isometry()
     assert U.shape == (D * D, D)
     # converged pairs: residual at most 1e-12 of the largest eigenvalue; the
-    # vectors are products over p <= 96 of columns orthonormal to 96 x 4e-15
+    # vectors are products over p <= 96 of columns orthonormal to 96 x 4e-15 (later rotations of the
+    # Jacobi's last sweep included: 8e-15 a pair at most where tried, few pairs near it)
     check_pairs(E, U, 4e-13, 1.1e-12)
     s.close()
 

@@ -62,9 +62,8 @@ def test_fp64_odd_rows(gpu_lib, M, N, K):
     check_product(M, N, K, "fp64")
 
 
-# ragged K in the split precisions, K split over the waves of 32 x 32 tiles up to
-# 192 tiles of 64 x 64 and from K = 32: partial tiles, fewer groups of 16 k than
-# waves, a partial last group, one past the end of the rule
+# ragged K in the split precisions, few tiles: partial ones, a few K steps and
+# many, a partial last step, 192 tiles of 64 x 64 and one row more
 @pytest.mark.parametrize("M,N,K", [(1, 1, 33), (31, 33, 47), (32, 64, 127), (33, 65, 129), (441, 441, 441), (100, 70, 1025),
                                    (768, 1024, 63), (769, 1024, 63), (12288, 21, 41)])
 @pytest.mark.parametrize("precision", ["bf16x3", "bf16x6"])
@@ -81,7 +80,8 @@ def test_panel_operands(gpu_lib, M, N, K, precision):
     check_product(M, N, K, precision, role="y", panel=True)
 
 
-# FP32: K split over the waves up to 256 tiles of 64 x 64, and one past the rule
+# FP32, few tiles: partial ones, a few K steps and many, 256 tiles of 64 x 64 and
+# one row more
 @pytest.mark.parametrize("M,N,K", [(1, 1, 32), (31, 33, 33), (33, 65, 1025), (576, 576, 576), (100, 70, 31),
                                    (1024, 1024, 47), (1025, 1024, 64), (16384, 24, 100)])
 def test_fp32_split_k(gpu_lib, M, N, K):
